@@ -54,7 +54,8 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kChunkCands = 2048;   // candidates per work item
+constexpr int kChunkCands = 2048;   // most candidates of a work item (scan_chunk)
+constexpr int kChunkMin = 64;       // least: one tile per wavefront
 constexpr int kGroupQ = 8;          // queries per work item (16 MFMA rows / 2)
 constexpr int kScanThreads = 256;
 constexpr int kScaleRegs = kChunkCands / 256;   // scale words per lane: 4 tiles of a wave each
@@ -82,8 +83,35 @@ struct ScanWs {
   size_t bytes;
 };
 
+// Work items of a call, at most: (groups of <= 8 queries) x (chunks of the
+// longest list); groups <= npairs / 8 + (number of probed lists), and no more
+// than one per pair.
+static int64_t scan_max_items(int Q, int nprobe, int nlist, int max_list, int chunk) {
+  const int64_t npairs = int64_t(Q) * nprobe;
+  const int64_t groups = npairs / kGroupQ + std::min<int64_t>(nlist, npairs);
+  return groups * std::max<int64_t>(1, (int64_t(max_list) + chunk - 1) / chunk);
+}
+
+// Most candidates of a work item.  2,048 where the call has items enough for
+// the persistent grid (about 512 workgroups); fewer where it has not, so that
+// every workgroup gets one: a 2,048-candidate item is 32 tiles in turn per
+// wavefront, about 20 us at any dimension, which a call of a few lists would
+// wait for with most of the chip idle.  Lists are taken to be half as long as
+// the longest.  A power of two: the planning kernels divide by it for every
+// list.  One query, 4 lists of about 625 candidates at D = 128: scan
+// kernel 26.8 us with 2,048-candidate items on
+// the full grid, 6.3 us with these.
+static int scan_chunk(int Q, int nprobe, int nlist, int max_list) {
+  const int64_t npairs = int64_t(Q) * nprobe;
+  const int64_t groups = std::min<int64_t>(npairs, npairs / kGroupQ + nlist);
+  const int64_t per = groups * (int64_t(max_list) / 2) / 512;
+  int chunk = kChunkMin;
+  while (chunk < kChunkCands && chunk < per) chunk *= 2;
+  return chunk;
+}
+
 static ScanWs scan_ws_layout(void *base, int Q, int nprobe, int nlist, int d_pad,
-                             int max_list, int k) {
+                             int max_list, int chunk) {
   ScanWs w{};
   char *p = static_cast<char *>(base);
   size_t off = 0;
@@ -103,17 +131,10 @@ static ScanWs scan_ws_layout(void *base, int Q, int nprobe, int nlist, int d_pad
   w.prefix = reinterpret_cast<int32_t *>(take(size_t(Q) * nprobe * 4));
   w.totals = reinterpret_cast<int32_t *>(take(size_t(Q) * 4));
   w.work = reinterpret_cast<int32_t *>(take(kQueues * kQueueStride * 4));
-  {
-    // work items <= (groups of <= 8 queries) x (chunks of the longest list);
-    // groups <= npairs / 8 + (number of probed lists)
-    const int64_t npairs = int64_t(Q) * nprobe;
-    const int64_t groups = npairs / kGroupQ + std::min<int64_t>(nlist, npairs);
-    const int64_t chunks = std::max<int64_t>(1, (int64_t(max_list) + kChunkCands - 1) / kChunkCands);
-    w.items = reinterpret_cast<int4 *>(take(size_t(groups * chunks) * 2 * sizeof(int4)));
-  }
+  w.items = reinterpret_cast<int4 *>(
+      take(size_t(scan_max_items(Q, nprobe, nlist, max_list, chunk)) * 2 * sizeof(int4)));
   w.stride = (int64_t(nprobe) * max_list + 63) / 64 * 64;
   w.scores = reinterpret_cast<float *>(take(size_t(Q) * size_t(w.stride) * 4));
-  (void)k;
   w.bytes = off;
   return w;
 }
@@ -181,10 +202,10 @@ __device__ __forceinline__ void query_prefix(const int32_t *__restrict__ probe_i
 }
 
 // Candidates per work item of a list of sz > 0 candidates: the list is split
-// into the fewest chunks of at most kChunkCands, of equal size rounded up to
-// whole tiles, so the items of a list have (almost) equal work.
-__device__ __forceinline__ int item_cands(int sz) {
-  const int nch = (sz + kChunkCands - 1) / kChunkCands;
+// into the fewest chunks of at most 2^chunk_log (>= 16), of equal size
+// rounded up to whole tiles, so the items of a list have (almost) equal work.
+__device__ __forceinline__ int item_cands(int sz, int chunk_log) {
+  const int nch = (sz + (1 << chunk_log) - 1) >> chunk_log;
   return ((sz + nch - 1) / nch + 15) & ~15;
 }
 constexpr int kSizeClasses = kChunkCands / 16;   // item size class = cands / 16 - 1
@@ -196,10 +217,10 @@ static_assert(kPlanRange / kPlanThreads == 16, "per-thread list batch");
 
 // Work items of a list with cp pairs and `size` candidates (groups of <= 8
 // queries x chunks) and their size class.
-__device__ __forceinline__ int list_items(int cp, int size, int max_list, int &cls) {
+__device__ __forceinline__ int list_items(int cp, int size, int max_list, int chunk_log, int &cls) {
   const int sz = max(0, min(size, max_list));
   if (cp <= 0 || sz <= 0) return 0;
-  const int ic = item_cands(sz);
+  const int ic = item_cands(sz, chunk_log);
   cls = ic / 16 - 1;
   return ((cp + kGroupQ - 1) / kGroupQ) * ((sz + ic - 1) / ic);
 }
@@ -218,7 +239,7 @@ struct PlanSmem {
 // class starts are known, item_off[L] holds the list's item count.
 __device__ void plan_lists(PlanSmem &sm, const int32_t *__restrict__ probe_ids, int npairs,
                            const int32_t *__restrict__ sizes, int nlist, int max_list,
-                           int32_t *__restrict__ counts, int32_t *__restrict__ pair_off,
+                           int chunk_log, int32_t *__restrict__ counts, int32_t *__restrict__ pair_off,
                            int32_t *__restrict__ item_off, int32_t *__restrict__ cursor,
                            int32_t *__restrict__ work) {
   const int t = threadIdx.x;
@@ -255,7 +276,7 @@ __device__ void plan_lists(PlanSmem &sm, const int32_t *__restrict__ probe_ids, 
       const int cp = sm.cnt[a + u];
       sum += cp;
       int cls = 0;
-      const int ni = list_items(cp, szv[u], max_list, cls);
+      const int ni = list_items(cp, szv[u], max_list, chunk_log, cls);
       if (ni > 0) atomicAdd(&sm.hist[cls], ni);
       item_off[L0 + a + u] = ni;
     }
@@ -320,7 +341,7 @@ __device__ void plan_lists(PlanSmem &sm, const int32_t *__restrict__ probe_ids, 
       const int L = base + u * kPlanThreads + t;
       if (L >= nlist) break;
       // a list with items has 0 < size; its class depends on the size only
-      const int cls = item_cands(max(1, min(szv[u], max_list))) / 16 - 1;
+      const int cls = item_cands(max(1, min(szv[u], max_list)), chunk_log) / 16 - 1;
       item_off[L] = niv[u] > 0 ? atomicAdd(&sm.start[cls], niv[u]) : 0;
     }
   }
@@ -331,14 +352,14 @@ __device__ void plan_lists(PlanSmem &sm, const int32_t *__restrict__ probe_ids, 
 __global__ void __launch_bounds__(kPlanThreads) k_plan_a(
     const float *__restrict__ q_rot, int Q, int D, int d_pad, _Float16 *__restrict__ qh,
     _Float16 *__restrict__ ql, float *__restrict__ qinv, const int32_t *__restrict__ probe_ids,
-    int nprobe, int nlist, const int32_t *__restrict__ sizes, int max_list,
+    int nprobe, int nlist, const int32_t *__restrict__ sizes, int max_list, int chunk_log,
     int32_t *__restrict__ prefix, int32_t *__restrict__ totals, int32_t *__restrict__ counts,
     int32_t *__restrict__ pair_off, int32_t *__restrict__ item_off, int32_t *__restrict__ cursor,
     int32_t *__restrict__ work) {
   __shared__ PlanSmem sm;
   if (blockIdx.x == 0) {
-    plan_lists(sm, probe_ids, Q * nprobe, sizes, nlist, max_list, counts, pair_off, item_off,
-               cursor, work);
+    plan_lists(sm, probe_ids, Q * nprobe, sizes, nlist, max_list, chunk_log, counts, pair_off,
+               item_off, cursor, work);
     return;
   }
   const int q = (blockIdx.x - 1) * kPlanQueries + (threadIdx.x >> 6);
@@ -361,7 +382,8 @@ constexpr int kPlanBThreads = 256;
 __global__ void __launch_bounds__(kPlanBThreads) k_plan_b(
     const int32_t *__restrict__ probe_ids, int npairs, int nlist,
     const int32_t *__restrict__ counts, const int32_t *__restrict__ sizes,
-    const int64_t *__restrict__ list_offsets, int max_list, const int32_t *__restrict__ pair_off,
+    const int64_t *__restrict__ list_offsets, int max_list, int chunk_log,
+    const int32_t *__restrict__ pair_off,
     const int32_t *__restrict__ item_off, int32_t *__restrict__ cursor,
     int32_t *__restrict__ pairs, int4 *__restrict__ items) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -374,7 +396,7 @@ __global__ void __launch_bounds__(kPlanBThreads) k_plan_b(
   const int c = counts[L];
   const int sz = max(0, min(sizes[L], max_list));
   if (c <= 0 || sz <= 0) return;
-  const int ic = item_cands(sz);
+  const int ic = item_cands(sz, chunk_log);
   const int nch = (sz + ic - 1) / ic;
   const int ngr = (c + kGroupQ - 1) / kGroupQ;
   const int it0 = item_off[L];
@@ -714,6 +736,7 @@ __global__ void __launch_bounds__(kScanThreads, 2) k_scan(ScanArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar loop control
   const int nwaves = kScanThreads / 64;
   const uint32_t lane4 = uint32_t(lane) * 4u;
+  const int n_items_v = a.item_off[a.nlist];   // arrives while the table is filled
 
   // replicate the table: entry e of copy l at word (e * kCopies + l) *
   // kWords; a byte entry is the compact entries of its low and high nibbles.
@@ -735,9 +758,12 @@ __global__ void __launch_bounds__(kScanThreads, 2) k_scan(ScanArgs a) {
       for (int w = 0; w < T::kWords; ++w) dtab[idx * T::kWords + w] = a.dtab[e * T::kWords + w];
     }
   }
+  // a workgroup beyond the number of items would only search eight empty
+  // queues (and contend for their counters with those that have work)
+  const int n_items = __builtin_amdgcn_readfirstlane(n_items_v);
+  if (int(blockIdx.x) >= n_items) return;
   __syncthreads();
 
-  const int n_items = __builtin_amdgcn_readfirstlane(a.item_off[a.nlist]);
   const int m = lane & 15;           // A row / B column of this lane
   const int kq = lane >> 4;          // k-quarter: coordinates 8 kq .. 8 kq + 7 of a chunk
   // Dynamic schedule: a workgroup takes items (largest first) from the queue
@@ -755,12 +781,13 @@ __global__ void __launch_bounds__(kScanThreads, 2) k_scan(ScanArgs a) {
     return uint32_t(atomicInc(reinterpret_cast<unsigned *>(a.work + x * kQueueStride), 0x7fffffffu));
   };
   // item of ticket j of the current queue, moving on to the next queues
-  // while the current one is empty; n_items when every queue is
+  // while the current one is empty; n_items when every queue is.  A queue
+  // whose first item does not exist is passed over without an atomic.
   auto resolve = [&](uint32_t j) {
     int64_t it = queue_item(q_cur, j);
     while (it >= n_items && ++q_tried < kQueues) {
       q_cur = (q_cur + 1) & (kQueues - 1);
-      it = queue_item(q_cur, draw(q_cur));
+      it = queue_item(q_cur, 0) < n_items ? queue_item(q_cur, draw(q_cur)) : n_items;
     }
     return int(it < n_items ? it : n_items);
   };
@@ -1315,7 +1342,8 @@ size_t rslm_scan_topk_workspace(const rslm_plan *p, const rslm_index *idx, int32
                                 int32_t nprobe, int32_t k) {
   if (!p || !idx || Q < 0 || nprobe < 1 || idx->nlist < 1 || idx->max_list_size < 0 || k < 1)
     return 0;
-  return scan_ws_layout(nullptr, Q, nprobe, idx->nlist, p->codec.d_pad, idx->max_list_size, k)
+  return scan_ws_layout(nullptr, Q, nprobe, idx->nlist, p->codec.d_pad, idx->max_list_size,
+                        scan_chunk(Q, nprobe, idx->nlist, idx->max_list_size))
       .bytes;
 }
 
@@ -1358,24 +1386,32 @@ int rslm_scan_topk(const rslm_plan *p, const rslm_index *idx, const float *q_rot
       }
     if (n_pass == 0) return RSLM_ERR_UNSUPPORTED;
   }
-  const size_t need = rslm_scan_topk_workspace(p, idx, Q, nprobe, k);
-  if (!ws || ws_bytes < need) return RSLM_ERR_WORKSPACE;
   const int nlist = idx->nlist;
   const int d_pad = p->codec.d_pad;
-  ScanWs w = scan_ws_layout(ws, Q, nprobe, nlist, d_pad, idx->max_list_size, k);
+  // smaller items need more descriptors: a workspace that has room only for
+  // those of full-size items gets full-size items
+  int chunk = scan_chunk(Q, nprobe, nlist, idx->max_list_size);
+  if (!ws) return RSLM_ERR_WORKSPACE;
+  ScanWs w = scan_ws_layout(ws, Q, nprobe, nlist, d_pad, idx->max_list_size, chunk);
+  if (ws_bytes < w.bytes) {
+    chunk = kChunkCands;
+    w = scan_ws_layout(ws, Q, nprobe, nlist, d_pad, idx->max_list_size, chunk);
+    if (ws_bytes < w.bytes) return RSLM_ERR_WORKSPACE;
+  }
+  const int chunk_log = 31 - __builtin_clz(unsigned(chunk));
   hipStream_t s = as_stream(stream);
   const int npairs = Q * nprobe;
   int st;
   hipLaunchKernelGGL(k_plan_a, dim3((Q + kPlanQueries - 1) / kPlanQueries + 1), dim3(kPlanThreads),
                      0, s, q_rot, Q,
                      p->rot.D, d_pad, w.qh, w.ql, w.qinv, probe_ids, nprobe, nlist,
-                     idx->list_sizes, idx->max_list_size, w.prefix, w.totals, w.counts,
+                     idx->list_sizes, idx->max_list_size, chunk_log, w.prefix, w.totals, w.counts,
                      w.pair_off, w.item_off, w.cursor, w.work);
   if ((st = check_launch())) return st;
   const int64_t planb_threads = std::max<int64_t>(npairs, int64_t(nlist) * 64);
   hipLaunchKernelGGL(k_plan_b, dim3(unsigned((planb_threads + kPlanBThreads - 1) / kPlanBThreads)),
                      dim3(kPlanBThreads), 0, s, probe_ids, npairs, nlist, w.counts,
-                     idx->list_sizes, idx->list_offsets, idx->max_list_size, w.pair_off,
+                     idx->list_sizes, idx->list_offsets, idx->max_list_size, chunk_log, w.pair_off,
                      w.item_off, w.cursor, w.pairs, w.items);
   if ((st = check_launch())) return st;
 
@@ -1411,7 +1447,8 @@ int rslm_scan_topk(const rslm_plan *p, const rslm_index *idx, const float *q_rot
   // byte tables of 2 and 1 bits from 24 chunks up)
   const bool big_table = p->codec.bits == 4 || (p->codec.bits <= 2 && nc_pass >= 24);
   const int wg_per_cu = big_table ? 2 : 4;
-  const dim3 grid(unsigned(cu_count() * wg_per_cu));
+  const dim3 grid(unsigned(std::min<int64_t>(
+      cu_count() * wg_per_cu, scan_max_items(Q, nprobe, nlist, idx->max_list_size, chunk))));
   switch (p->codec.bits) {
     case 4:
       if (a.lead > 0) launch_scan_bits<4, true>(nc_pass, n_pass > 1, grid, s, a);
