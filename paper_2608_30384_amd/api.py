@@ -18,9 +18,17 @@ def _ptr(t):
     return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
 
 
+def _raw_stream(stream=None, device=None):
+    """The hipStream_t of `stream`, or of the current stream of `device` (the
+    current device if None), without building a torch.cuda.Stream object."""
+    if stream is not None:
+        return stream.cuda_stream
+    index = device.index if device is not None else None
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
+
+
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    return C.c_void_p(_raw_stream(stream))
 
 
 def _need(t, dtype, name):
@@ -46,10 +54,10 @@ class _Workspace:
         self._bufs = {}
 
     def get(self, nbytes, device, key, stream=None):
-        s = stream if stream is not None else torch.cuda.current_stream(device)
-        k = (str(device), s.cuda_stream, key)
+        k = (device, _raw_stream(stream, device), key)
         b = self._bufs.get(k)
         if b is None or b.numel() < nbytes:
+            s = stream if stream is not None else torch.cuda.current_stream(device)
             with torch.cuda.stream(s):
                 b = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
             self._bufs[k] = b
