@@ -1,0 +1,8 @@
+// Encoder on 16-lane rows: 1-bit codec, with a 2-bit RSLM second stage.
+#include "encode_rows.h"
+
+namespace rslm {
+
+template void launch_encode_rows<1, false, true>(const EncodeArgs &, hipStream_t);
+
+}  // namespace rslm

@@ -12,6 +12,7 @@
 // trips (3 + 3 + 1 stages).  The encoder fuses residual, rotation, EVT
 // scale, Lloyd-Max assignment, norm correction, both 16-bit scales, packing
 // into the scan tile layout and the rotated second residual.
+#include "encode_rows.h"
 #include "rslm_internal.h"
 
 namespace rslm {
@@ -763,16 +764,47 @@ int rslm_fwht(const rslm_plan *p, const float *x, float *y, int64_t n, int inver
   return check_launch();
 }
 
+// Whether the encoder on 16-lane rows takes a call: D >= 128, quantiser tables
+// that fit it (1-D grids of at most kQuantBuckets buckets, cell lists for 2-D
+// codebooks), and a 2-bit second stage if any.  No alignment beyond the
+// element types' is assumed.
+static bool encode_on_rows(const rslm_plan *p, const rslm_plan *p2) {
+  const CodecParams &cp = p->codec;
+  if (!rows_ok(p->rot)) return false;
+  if (cp.g == 1 && (cp.qn < 1 || cp.qn > kQuantBuckets)) return false;
+  if (cp.lead > 0 && (cp.qn_lead < 1 || cp.qn_lead > kQuantBuckets)) return false;
+  if (cp.g == 2 && !cp.g2tab) return false;
+  if (p2 && (p2->codec.g != 2 || p2->codec.lead > 0 || !p2->codec.g2tab)) return false;
+  return true;
+}
+
 static int encode_impl(const rslm_plan *p, const rslm_plan *p2, const float *x, int64_t n_rows,
                        const int64_t *src_row, const int32_t *rec_list, int64_t n_records,
                        const float *centroids, const float *centroids_rot, int32_t nlist,
                        uint8_t *codes, uint32_t *scales, float *resid_rot, uint8_t *codes2,
                        uint32_t *scales2, const float *sq8_lo, const float *sq8_hi,
                        hipStream_t s) {
-  if (launch_encode_reg(p, p2, x, n_rows, src_row, rec_list, n_records, centroids,
-                        centroids_rot, nlist, codes, scales, resid_rot, codes2, scales2, sq8_lo,
-                        sq8_hi, s))
+  if (encode_on_rows(p, p2)) {
+    const EncodeArgs a{x,         n_rows, src_row,   rec_list, n_records, centroids, centroids_rot,
+                       nlist,     codes,  scales,    resid_rot, codes2,   scales2,   sq8_lo,
+                       sq8_hi,    p->rot, p->codec,  p2 ? p2->codec : p->codec};
+    const bool lite = p->codec.lead > 0;
+    switch (p->codec.bits) {
+      case 4:
+        if (lite) p2 ? launch_encode_rows<4, true, true>(a, s) : launch_encode_rows<4, true, false>(a, s);
+        else p2 ? launch_encode_rows<4, false, true>(a, s) : launch_encode_rows<4, false, false>(a, s);
+        break;
+      case 3:
+        p2 ? launch_encode_rows<3, false, true>(a, s) : launch_encode_rows<3, false, false>(a, s);
+        break;
+      case 2:
+        p2 ? launch_encode_rows<2, false, true>(a, s) : launch_encode_rows<2, false, false>(a, s);
+        break;
+      default:
+        p2 ? launch_encode_rows<1, false, true>(a, s) : launch_encode_rows<1, false, false>(a, s);
+    }
     return check_launch();
+  }
   const int D = p->rot.D;
   const int dstride = lds_floats(D);
   // vectors per wavefront: a butterfly round has D / 8 groups, so give a

@@ -132,18 +132,10 @@ bool device_ok();                    // current device is gfx950
 
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
-// Register-resident rotation / 1-D encoder for D = 128 NB (rotate_reg.hip);
-// false when the plan is not handled there.
+// Register-resident rotation for D = 128 NB (rotate_reg.hip); false when the
+// plan is not handled there.
 bool launch_rotate_reg(const rslm_plan *p, const float *x, float *y, int64_t n, int inverse,
                        hipStream_t s);
-// Optional second output: the RSLM rescoring stage of rslm_encode_two_stage
-// (p2, codes2, scales2), or the SQ8 codes of rslm_encode_sq8 (sq8_lo,
-// sq8_hi, codes2); neither: p2 == nullptr and sq8_lo == nullptr.
-bool launch_encode_reg(const rslm_plan *p, const rslm_plan *p2, const float *x, int64_t n_rows,
-                       const int64_t *src_row, const int32_t *rec_list, int64_t n_records,
-                       const float *cen, const float *cen_rot, int nlist, uint8_t *codes,
-                       uint32_t *scales, float *resid, uint8_t *codes2, uint32_t *scales2,
-                       const float *sq8_lo, const float *sq8_hi, hipStream_t s);
 
 // ---- device helpers ------------------------------------------------------
 
