@@ -914,6 +914,8 @@ int rslm_decode(const rslm_plan *p, const uint8_t *codes, const uint32_t *scales
   if (n == 0) return RSLM_OK;
   if (!codes || !scales || !out) return RSLM_ERR_INVALID_ARG;
   if (centroids && (!rec_list || nlist < 1)) return RSLM_ERR_INVALID_ARG;
+  if (launch_decode_rows(p, codes, scales, n, rec_list, centroids, nlist, out, as_stream(stream)))
+    return check_launch();
   const int D = p->rot.D;
   const int dstride = lds_floats(D);
   int waves = 4;
