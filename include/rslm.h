@@ -272,6 +272,9 @@ int rslm_score(const rslm_plan *plan, const uint8_t *records, int64_t n_pool,
  *                  n x nprobe (out_scores = the dots).
  *   x: n x dim, centroids: nlist x dim (float32).  nlist <= 65536,
  *   nprobe <= min(nlist, 1024).
+ *   Large IVF_ASSIGN_L2 calls keep the centres' float16 halves in the
+ *   workspace; one of 4 nlist bytes (rounded to 256) is accepted as well and
+ *   takes the float32 kernels.
  * ------------------------------------------------------------------------ */
 #define IVF_ASSIGN_L2 0
 #define IVF_PROBE_IP 1
@@ -291,8 +294,8 @@ int ivf_assign_probe(const float *x, int64_t n, int32_t dim,
  * holds once per GPU it runs on until the process ends.  This call allocates
  * nothing (no hipMalloc / hipFree, no allocating library routine); the
  * caller passes inputs and outputs as for ivf_assign_probe.
- *   Sizes whose workspace (ivf_assign_probe_workspace) exceeds the limit --
- *   probing needs n * nlist * 4 bytes plus 4 * nlist rounded to 256 -- return
+ *   Sizes whose least workspace exceeds the limit -- probing needs n * nlist *
+ *   4 bytes plus 4 * nlist rounded to 256, assignment the latter -- return
  *   RSLM_ERR_WORKSPACE before any launch.
  *   Every call on one GPU shares that GPU's scratch: calls that overlap in
  *   time on one GPU (different streams, threads or processes' graphs) race

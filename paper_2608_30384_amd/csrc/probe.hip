@@ -393,6 +393,409 @@ __global__ void __launch_bounds__(256) k_assign_mfma(const float *__restrict__ x
     }
 }
 
+// ------------------------------------------------ assignment on split float16
+// Large assignments: the float32 matrix instructions are the limit (157
+// TFLOP/s; k_assign_mfma runs at 125), so each operand is split into two
+// float16 halves, v s = hi + lo with s a power of two per row that puts the
+// row's largest magnitude in [2^14, 2^15), and <x, c> is accumulated in
+// float32 as hi hi + hi lo + lo hi on v_mfma_f32_16x16x32_f16 (16 times the
+// float32 rate per product).  hi + lo carries 22 to 23 significant bits (and
+// never less than 2^-39 of the row's largest element); what is dropped, lo lo,
+// is below 2^-22 of each product.  Both are smaller than the roundings of the
+// float32 sum, which has D / 32 steps here against D / 4 there.  Error of the
+// distances against float64 (2-norm, relative): 524,288 x 768 by 4,096 1.7e-7,
+// float32 kernel 8.9e-7; 100,000 x 1,447 by 3,000 2.2e-7 and 1.5e-6; 524,288 x
+// 100 by 4,096 1.5e-7 and 4.7e-7.
+//
+// A workgroup of eight wavefronts owns 256 rows of x and walks its share of
+// the centres in tiles of 256: with both sides at 256 each operand is read
+// from L2 once per 256 rows of the other, which is what the matrix cores leave
+// time for.  The centres are split once per call (k_split_centres), the rows
+// of x as they are staged (they are too many to keep).  k goes through LDS in
+// slabs of 32, two buffers, one barrier per slab.  Centres are the M side, so
+// a lane holds 32 centres of each of four rows and keeps four running minima.
+// 1,048,576 x 768 by 4,096: 52.6 ms on the float32 kernel, 20.2 ms here (327
+// TFLOP/s of distances, 981 TFLOP/s of float16 products; a large bf16 library
+// product runs at 1,370 on the same card).  The same tiles with the centres
+// staged through registers 30.6 ms, with two slabs of both operands in
+// registers 38.8 ms (spills).
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+constexpr int kSpM = 256, kSpN = 256, kSpK = 32, kSpThreads = 512;
+constexpr int kSpRow = 4 * kSpK;       // bytes per LDS row: hi, then lo
+constexpr int kWaitVm0 = 0x0F70;       // s_waitcnt vmcnt(0), the other counters free
+constexpr int kSlowRow = int(0x80000000);   // id of a row left to k_assign_finish
+
+struct __attribute__((packed, aligned(4))) F4u {
+  float x, y, z, w;
+};
+
+// Power of two s with m s in [2^14, 2^15) (m > 0 finite; the exponent is
+// clamped where s would not be a normal number).
+__device__ __forceinline__ float split_scale(float m) {
+  if (!(m > 0.f) || !(m < __builtin_inff())) return 1.f;
+  return ldexpf(1.f, max(-126, min(126, 14 - ilogbf(m))));
+}
+
+// One wavefront per centre (nlist rounded up to whole tiles): ||c||^2 (summed
+// in float64; +inf past nlist, so padding is never nearest), -2 / s, and the
+// halves, slab by slab (32 hi, then 32 lo, zero past D).
+__global__ void __launch_bounds__(256) k_split_centres(const float *__restrict__ cen, int nlist, int D,
+                                                       int n_slab, float *__restrict__ cnorm,
+                                                       float *__restrict__ cmul,
+                                                       _Float16 *__restrict__ split) {
+  const int lane = threadIdx.x & 63;
+  const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const float *row = cen + int64_t(c) * D;
+  const bool in = c < nlist;
+  double sum = 0.0;
+  float m = 0.f;
+  for (int i = lane; in && i < D; i += 64) {
+    const float v = row[i];
+    sum += double(v) * double(v);
+    m = fmaxf(m, fabsf(v));
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  const float sc = split_scale(wave_max(m));
+  if (lane == 0) {
+    cnorm[c] = in ? float(sum) : __builtin_inff();
+    cmul[c] = -2.f / sc;
+  }
+  _Float16 *out = split + int64_t(c) * n_slab * (2 * kSpK);
+  for (int i = lane; i < n_slab * kSpK; i += 64) {
+    const float v = (in && i < D) ? row[i] * sc : 0.f;
+    const _Float16 h = static_cast<_Float16>(v);
+    out[(i / kSpK) * (2 * kSpK) + i % kSpK] = h;
+    out[(i / kSpK) * (2 * kSpK) + kSpK + i % kSpK] = static_cast<_Float16>(v - static_cast<float>(h));
+  }
+}
+
+// Workgroup (rows, share): nearest of the centres [tiles t0, t1) of 256 for
+// 256 rows; (distance without ||x||^2, id) to best_v / best_i at [share][row].
+__global__ void __launch_bounds__(kSpThreads, 2) k_assign_split(
+    const float *__restrict__ x, int64_t n, int D, int n_slab, const float *__restrict__ cnorm,
+    const float *__restrict__ cmul, const _Float16 *__restrict__ split, int n_tiles,
+    int tiles_per_share, float *__restrict__ best_v, int32_t *__restrict__ best_i) {
+  // rows of 128 bytes (32 hi, 32 lo): x, then centres; the eight 16-byte units
+  // of row r are stored at unit ^ (r % 8), which spreads a column of units
+  // over the banks without padding (the centres are written by lanes in order)
+  __shared__ __align__(128) uint8_t lds[2][(kSpM + kSpN) * kSpRow];
+  __shared__ float xscale[kSpM];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m = lane & 15, h = lane >> 4;
+  const int wx = (wave & 3) * 64, wc = (wave >> 2) * 128;   // this wave's rows and centres
+  const int64_t r0 = int64_t(blockIdx.x) * kSpM;
+  const int t0 = blockIdx.y * tiles_per_share, t1 = min(n_tiles, t0 + tiles_per_share);
+  // largest magnitude of each row: 32 rows per wavefront, four in flight
+  for (int q = 0; q < 32; q += 4) {
+    float mx[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int k = lane; k < D; k += 64) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t r = min(r0 + wave * 32 + q + u, n - 1);
+        mx[u] = fmaxf(mx[u], fabsf(x[r * D + k]));
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      mx[u] = wave_max(mx[u]);
+      // an infinite row is marked (by a zero scale) and left to k_assign_finish
+      if (lane == 0) xscale[wave * 32 + q + u] = mx[u] < __builtin_inff() ? split_scale(mx[u]) : 0.f;
+    }
+  }
+  __syncthreads();
+  // Staging, in 16-byte units u < 4 per thread.  x: four coordinates (unit tid
+  // % 8) of row tid / 8 + 64 u, through registers and the split.  Centres:
+  // straight from memory into LDS, 64 lanes filling eight rows.
+  const int srow = tid >> 3, scol = (tid & 7) * 4;
+  const float *xrow[4];
+  float sc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    xrow[u] = x + min(r0 + srow + 64 * u, n - 1) * D;
+    sc[u] = xscale[srow + 64 * u];
+  }
+  const int xhi = ((((tid & 7) >> 1) ^ (srow & 7)) * 16) + (tid & 1) * 8;   // byte in the row
+  const int xlo = (((4 + ((tid & 7) >> 1)) ^ (srow & 7)) * 16) + (tid & 1) * 8;
+  float4 pa[4];
+  auto load_x = [&](int sl) {
+    const int k = sl * kSpK + scol;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (sl * kSpK + kSpK <= D) {   // uniform
+        const F4u v = *reinterpret_cast<const F4u *>(xrow[u] + k);
+        pa[u] = make_float4(v.x, v.y, v.z, v.w);
+      } else {
+        pa[u].x = k < D ? xrow[u][min(k, D - 1)] : 0.f;
+        pa[u].y = k + 1 < D ? xrow[u][min(k + 1, D - 1)] : 0.f;
+        pa[u].z = k + 2 < D ? xrow[u][min(k + 2, D - 1)] : 0.f;
+        pa[u].w = k + 3 < D ? xrow[u][min(k + 3, D - 1)] : 0.f;
+      }
+    }
+  };
+  auto store_x = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float v[4] = {pa[u].x * sc[u], pa[u].y * sc[u], pa[u].z * sc[u], pa[u].w * sc[u]};
+      half4_t hi, lo;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        hi[e] = static_cast<_Float16>(v[e]);
+        lo[e] = static_cast<_Float16>(v[e] - static_cast<float>(hi[e]));
+      }
+      uint8_t *px = &lds[buf][(srow + 64 * u) * kSpRow];
+      *reinterpret_cast<half4_t *>(px + xhi) = hi;
+      *reinterpret_cast<half4_t *>(px + xlo) = lo;
+    }
+  };
+  // the unit that lands in this lane's place, of row wave * 8 + lane / 8 + 64 u
+  const _Float16 *csrc = split + (int64_t(wave * 8 + (lane >> 3)) * n_slab) * (2 * kSpK) +
+                         ((lane & 7) ^ (lane >> 3)) * 8;
+  auto load_c = [&](int tile, int sl, int buf) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void *)(
+              csrc + (int64_t(tile * kSpN + 64 * u) * n_slab + sl) * (2 * kSpK)),
+          (__attribute__((address_space(3))) void *)(&lds[buf][(kSpM + wave * 8 + 64 * u) * kSpRow]),
+          16, 0, 0);
+  };
+  floatx4_t acc[8][4];
+  float best[4], inv[4];
+  int32_t bid[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    best[j] = 3.4e38f;
+    bid[j] = 0x7fffffff;
+    const float s = xscale[wx + 16 * j + m];
+    inv[j] = s > 0.f ? 1.f / s : 0.f;
+  }
+  // Slabs in one sequence over the tiles.  While slab s is multiplied, the
+  // centres of slab s + 1 go to LDS, the coordinates of x of slab s + 1 (loaded
+  // during s - 1) are split and stored, and those of slab s + 2 are loaded.
+  const int total = (t1 - t0) * n_slab;
+  const int hi_unit = (h ^ (m & 7)) * 16, lo_unit = ((4 + h) ^ (m & 7)) * 16;
+  int tile = t0, sl = 0;
+  load_c(t0, 0, 0);
+  load_x(0);
+  store_x(0);
+  load_x(n_slab > 1 ? 1 : 0);
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  __syncthreads();
+  for (int it = 0; it < total; ++it) {
+    const int buf = it & 1;
+    const bool last = sl + 1 == n_slab;
+    if (it + 1 < total) {
+      load_c(last ? tile + 1 : tile, last ? 0 : sl + 1, buf ^ 1);
+      store_x(buf ^ 1);
+      load_x((sl + 2) % n_slab);   // past the end: not stored
+    }
+    if (sl == 0) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    const uint8_t *px = &lds[buf][(wx + m) * kSpRow];
+    const uint8_t *pc = &lds[buf][(kSpM + wc + m) * kSpRow];
+    half8_t xh[4], xl[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      xh[j] = *reinterpret_cast<const half8_t *>(px + 16 * j * kSpRow + hi_unit);
+      xl[j] = *reinterpret_cast<const half8_t *>(px + 16 * j * kSpRow + lo_unit);
+    }
+    // a slab's products are summed from zero and then added once: the float32
+    // accumulator is rounded D / 32 times, not 3 D / 32
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const half8_t ch = *reinterpret_cast<const half8_t *>(pc + 16 * i * kSpRow + hi_unit);
+      const half8_t cl = *reinterpret_cast<const half8_t *>(pc + 16 * i * kSpRow + lo_unit);
+      floatx4_t t[4];
+      const floatx4_t zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cl, xh[j], zero, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ch, xl[j], t[j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ch, xh[j], t[j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] += t[j];
+    }
+    if (last) {
+      // lane (m, h) holds centres c0 + wc + 16 i + 4 h + e of rows wx + 16 j + m
+      const int c0 = tile * kSpN + wc + 4 * h;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float4 cn = *reinterpret_cast<const float4 *>(cnorm + c0 + 16 * i);
+        const float4 cm = *reinterpret_cast<const float4 *>(cmul + c0 + 16 * i);
+        const float cna[4] = {cn.x, cn.y, cn.z, cn.w}, cma[4] = {cm.x, cm.y, cm.z, cm.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float v = fmaf(acc[i][j][e], cma[e] * inv[j], cna[e]);   // ||c||^2 - 2 <x, c>
+            if (v < best[j]) {   // centres visited in increasing order
+              best[j] = v;
+              bid[j] = c0 + 16 * i + e;
+            }
+          }
+      }
+      ++tile;
+      sl = 0;
+    } else {
+      ++sl;
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);   // the centres are in LDS
+    __syncthreads();
+  }
+  // merge the four lanes and the two wavefronts holding a row: lexicographic
+  // (value, id)
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int off = 16; off < 64; off <<= 1) {
+      const float ov = __shfl_xor(best[j], off, 64);
+      const int oi = __shfl_xor(bid[j], off, 64);
+      if (ov < best[j] || (ov == best[j] && oi < bid[j])) {
+        best[j] = ov;
+        bid[j] = oi;
+      }
+    }
+  float *red_v = reinterpret_cast<float *>(lds[0]);   // the last slab was multiplied before a barrier
+  int32_t *red_i = reinterpret_cast<int32_t *>(red_v + kSpM);
+  if (wave >= 4 && h == 0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      red_v[wx + 16 * j + m] = best[j];
+      red_i[wx + 16 * j + m] = bid[j];
+    }
+  }
+  __syncthreads();
+  if (wave >= 4 || h) return;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int rl = wx + 16 * j + m;
+    if (r0 + rl >= n) continue;
+    if (red_v[rl] < best[j] || (red_v[rl] == best[j] && red_i[rl] < bid[j])) {
+      best[j] = red_v[rl];
+      bid[j] = red_i[rl];
+    }
+    const int64_t at = int64_t(blockIdx.y) * n + r0 + rl;
+    if (best_v) best_v[at] = best[j];
+    best_i[at] = inv[j] > 0.f ? bid[j] : kSlowRow;
+  }
+}
+
+// One wavefront per row: the best of the shares, and ||x||^2 + its value as
+// the distance.  A row with an infinite coordinate is compared with every
+// centre in float32.
+__global__ void __launch_bounds__(256) k_assign_finish(
+    const float *__restrict__ x, int64_t n, int D, const float *__restrict__ cen, int nlist,
+    const float *__restrict__ cnorm, int shares, const float *best_v, const int32_t *best_i,
+    int32_t *out_ids, float *out_d) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (row >= n) return;
+  float v = __builtin_inff();
+  int32_t id = 0x7fffffff;
+  for (int s = lane; s < shares; s += 64) {
+    const float ov = best_v ? best_v[int64_t(s) * n + row] : 0.f;
+    const int32_t oi = best_i[int64_t(s) * n + row];
+    if (oi == kSlowRow || (id != kSlowRow && (ov < v || (ov == v && oi < id)))) {
+      v = ov;
+      id = oi;
+    }
+  }
+  for (int off = 1; off < 64; off <<= 1) {
+    const float ov = __shfl_xor(v, off, 64);
+    const int32_t oi = __shfl_xor(id, off, 64);
+    if (oi == kSlowRow || (id != kSlowRow && (ov < v || (ov == v && oi < id)))) {
+      v = ov;
+      id = oi;
+    }
+  }
+  const float *xr = x + row * D;
+  if (id == kSlowRow) {
+    v = 3.4e38f;
+    id = 0x7fffffff;
+    for (int c = 0; c < nlist; ++c) {
+      float dot = 0.f;
+      for (int k = lane; k < D; k += 64) dot += xr[k] * cen[int64_t(c) * D + k];
+      dot = wave_sum(dot);
+      const float w = cnorm[c] - 2.f * dot;
+      if (w < v) {
+        v = w;
+        id = c;
+      }
+    }
+  }
+  if (out_d) {
+    double s = 0.0;
+    for (int k = lane * 4; k < D; k += 256) {
+      if (k + 4 <= D) {
+        const F4u q = *reinterpret_cast<const F4u *>(xr + k);
+        s += double(q.x) * q.x + double(q.y) * q.y + (double(q.z) * q.z + double(q.w) * q.w);
+      } else {
+        for (int e = k; e < D; ++e) s += double(xr[e]) * xr[e];
+      }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) out_d[row] = float(s + double(v));
+  }
+  if (lane == 0) out_ids[row] = id;
+}
+
+// Whether an assignment runs on split float16, and its workspace.
+struct SplitWs {
+  float *cnorm, *cmul;
+  _Float16 *split;
+  float *part_v;
+  int32_t *part_i;
+  int tiles, n_slab, shares, tiles_per_share;
+  size_t bytes;
+};
+static bool assign_on_split(int64_t n, int dim, int nlist) {
+  // Rows that are whole 16-byte runs have the float32 matrix kernel to beat:
+  // up to 128 centres half a tile of 256 or more is padding (us, float32
+  // against split: 65,536 x 512 by 128 113, 119; 1,011,082 x 922 by 188 18,536 on
+  // the vector ALU, 3,472), and below 128 rows there is too little work (64 x 768
+  // by 1,024 91, 104; 256 x 768 by 4,096 149, 105).  Other rows have a vector-ALU
+  // kernel, slower from a few microseconds of work on (4,573 x 230 by 21 87, 52;
+  // 20,000 x 1,501 by 16 1,114, 242).
+  if (dim % 4 == 0) return nlist > 128 && n >= 128;
+  return double(n) * double(nlist) * double(dim) >= 1e6;
+}
+static SplitWs assign_split_ws(void *base, int64_t n, int dim, int nlist) {
+  SplitWs w{};
+  char *p = static_cast<char *>(base);
+  size_t off = 0;
+  auto take = [&](size_t b) {
+    char *r = p ? p + off : nullptr;
+    off += (b + 255) / 256 * 256;
+    return r;
+  };
+  w.tiles = (nlist + kSpN - 1) / kSpN;
+  w.n_slab = (dim + kSpK - 1) / kSpK;
+  const size_t np = size_t(w.tiles) * kSpN;
+  // the centres are shared out where the rows alone leave compute units idle
+  const int64_t blocks = (n + kSpM - 1) / kSpM;
+  const int64_t want = std::min<int64_t>(w.tiles, (512 + blocks - 1) / blocks);
+  w.tiles_per_share = int((w.tiles + want - 1) / want);
+  w.shares = (w.tiles + w.tiles_per_share - 1) / w.tiles_per_share;
+  w.cnorm = reinterpret_cast<float *>(take(np * 4));
+  w.cmul = reinterpret_cast<float *>(take(np * 4));
+  w.split = reinterpret_cast<_Float16 *>(take(np * w.n_slab * 2 * kSpK * sizeof(_Float16)));
+  if (w.shares > 1) {
+    w.part_v = reinterpret_cast<float *>(take(size_t(w.shares) * n * 4));
+    w.part_i = reinterpret_cast<int32_t *>(take(size_t(w.shares) * n * 4));
+  }
+  w.bytes = off;
+  return w;
+}
+
 // Probe dots for many rows (D a multiple of 4, 16-byte aligned operands): one
 // 128 x 128 tile (tile128) per workgroup, written out.
 __global__ void __launch_bounds__(256) k_dots_big(const float *__restrict__ x, int n, int D,
@@ -676,13 +1079,21 @@ extern "C" {
 
 size_t ivf_assign_probe_workspace(int64_t n, int32_t dim, int32_t nlist, int32_t nprobe,
                                   int mode) {
-  (void)dim;
   (void)nprobe;
   if (n < 0 || nlist < 1) return 0;
   const size_t norms = (size_t(nlist) * sizeof(float) + 255) / 256 * 256;
+  if (mode == IVF_ASSIGN_L2 && dim >= 1 && nlist <= 65536 && assign_on_split(n, dim, nlist))
+    return assign_split_ws(nullptr, n, dim, nlist).bytes;
   if (mode == IVF_ASSIGN_L2) return norms;
   const size_t dots = size_t(n) * size_t(nlist) * sizeof(float);
   return norms + (dots + 255) / 256 * 256;
+}
+
+// The least a call accepts: the float32 kernels' scratch.
+static size_t probe_min_workspace(int64_t n, int32_t nlist, int mode) {
+  const size_t norms = (size_t(nlist) * sizeof(float) + 255) / 256 * 256;
+  if (mode == IVF_ASSIGN_L2) return norms;
+  return norms + (size_t(n) * size_t(nlist) * sizeof(float) + 255) / 256 * 256;
 }
 
 int ivf_assign_probe(const float *x, int64_t n, int32_t dim, const float *centroids,
@@ -696,9 +1107,28 @@ int ivf_assign_probe(const float *x, int64_t n, int32_t dim, const float *centro
   if (n == 0) return RSLM_OK;
   if (!x || !centroids || !out_ids || (mode == IVF_PROBE_IP && !out_scores))
     return RSLM_ERR_INVALID_ARG;
-  if (!ws || ws_bytes < ivf_assign_probe_workspace(n, dim, nlist, nprobe, mode))
-    return RSLM_ERR_WORKSPACE;
+  if (!ws || ws_bytes < probe_min_workspace(n, nlist, mode)) return RSLM_ERR_WORKSPACE;
   hipStream_t s = as_stream(stream);
+  if (mode == IVF_ASSIGN_L2 && (n + 255) / 256 <= 0x7fffffff && (n + 3) / 4 <= 0x7fffffff &&
+      assign_on_split(n, dim, nlist)) {
+    // (a workspace that has room for the norms only takes the float32 kernels)
+    const SplitWs w = assign_split_ws(ws, n, dim, nlist);
+    if (ws_bytes >= w.bytes && (reinterpret_cast<uintptr_t>(ws) & 15) == 0) {
+      hipLaunchKernelGGL(k_split_centres, dim3(unsigned(w.tiles * kSpN / 4)), dim3(256), 0, s,
+                         centroids, nlist, dim, w.n_slab, w.cnorm, w.cmul, w.split);
+      int st = check_launch();
+      if (st) return st;
+      float *bv = w.shares > 1 ? w.part_v : out_scores;
+      int32_t *bi = w.shares > 1 ? w.part_i : out_ids;
+      hipLaunchKernelGGL(k_assign_split, dim3(unsigned((n + kSpM - 1) / kSpM), unsigned(w.shares)),
+                         dim3(kSpThreads), 0, s, x, n, dim, w.n_slab, w.cnorm, w.cmul, w.split,
+                         w.tiles, w.tiles_per_share, bv, bi);
+      if ((st = check_launch())) return st;
+      hipLaunchKernelGGL(k_assign_finish, dim3(unsigned((n + 3) / 4)), dim3(256), 0, s, x, n, dim,
+                         centroids, nlist, w.cnorm, w.shares, bv, bi, out_ids, out_scores);
+      return check_launch();
+    }
+  }
   if (mode == IVF_ASSIGN_L2) {
     float *cnorm = static_cast<float *>(ws);
     hipLaunchKernelGGL(k_row_norms, dim3((nlist + 3) / 4), dim3(256), 0, s, centroids, nlist,
@@ -767,8 +1197,7 @@ int ivf_assign_probe_noalloc(const float *x, int64_t n, int32_t dim, const float
   if (n == 0) return RSLM_OK;
   if (!x || !centroids || !out_ids || (mode == IVF_PROBE_IP && !out_scores))
     return RSLM_ERR_INVALID_ARG;
-  const size_t need = ivf_assign_probe_workspace(n, dim, nlist, nprobe, mode);
-  if (need > kProbeScratchBytes) return RSLM_ERR_WORKSPACE;
+  if (probe_min_workspace(n, nlist, mode) > kProbeScratchBytes) return RSLM_ERR_WORKSPACE;
   int st = RSLM_OK;
   void *ws = scratch_of_current_device(&st);
   if (!ws) return st;
