@@ -569,6 +569,8 @@ int rslm_score(const rslm_plan *p, const uint8_t *records, int64_t n_pool, const
   if (n == 0 || Q == 0) return RSLM_OK;
   if (!records || !q_rot || !out) return RSLM_ERR_INVALID_ARG;
   const CodecParams &cp = p->codec;
+  if (launch_score_mfma(p, records, n_pool, ids, n, q_rot, Q, out, as_stream(stream)))
+    return check_launch();
   const int n_groups = (cp.n_sub + 7) / 8;
   const size_t shm = size_t(n_groups) * 8 * cp.g * sizeof(float);
   // workgroups of 256 records (16 per pass of the 16-lane groups)

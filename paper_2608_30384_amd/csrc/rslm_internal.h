@@ -136,6 +136,10 @@ inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s);
 // plan is not handled there.
 bool launch_rotate_reg(const rslm_plan *p, const float *x, float *y, int64_t n, int inverse,
                        hipStream_t s);
+// rslm_score on the matrix cores (scan.hip); false where it does not pay or
+// does not apply.
+bool launch_score_mfma(const rslm_plan *p, const uint8_t *records, int64_t n_pool, const int64_t *ids,
+                       int64_t n, const float *q_rot, int Q, float *out, hipStream_t s);
 // rslm_decode on 16-lane rows (decode_rows.hip); false below D = 128.
 bool launch_decode_rows(const rslm_plan *p, const uint8_t *codes, const uint32_t *scales, int64_t n,
                         const int32_t *rec_list, const float *cen, int nlist, float *out,

@@ -1275,6 +1275,218 @@ __global__ void __launch_bounds__(kStreamThreads) k_topk_stream(
   block_topk(row, n, k, f, out_s + int64_t(q) * k, out_i + int64_t(q) * k, ss);
 }
 
+// ------------------------------------------------- OneToMany on the matrix cores
+// rslm_score for D <= 1,024 (32 chunks; not Rslm4Lite): the scan's decode table
+// and products on packed records.  Lane (kq, m) of a wavefront takes the kq-th
+// quarter of record m of 16, one contiguous run of bytes whose 8-coordinate
+// groups are the lane's chunks; the query's coordinates are dealt to the A rows
+// in the same order, so no code moves between lanes.  A wavefront scores four
+// queries at once: rows 4 q + {0, 1, 2} hold the scaled query in three float16
+// parts (33 bits, more than float32 has), row 4 q + 3 is zero.  With one query
+// 13 of the 16 rows idle, and still the decode (one v_perm and one
+// conflict-free LDS read per two 4-bit codes, where a lookup and a
+// multiply-add per code took ten instructions) leaves memory as the bound.
+// Us, k_score_reg against this: one query, 16,777,216 of D = 256, 4 bits 1,276, 817;
+// 4,000,000 gathered ones 370, 171; 3,000,000 of 1 bit 173, 57; 2,000,000 of D = 768
+// 616, 231; twelve queries, 500,000 of D = 945, 2 bits 1,245, 131.  Error against
+// float64 (2-norm, relative) 1.2e-7 and 1.3e-7 at D = 256, 1.8e-7 both at 768.
+struct ScoreArgs {
+  const uint8_t *records;
+  int64_t pool_bytes, n_pool;
+  const int64_t *ids;
+  int64_t n;
+  const float *q_rot;
+  int Q, D, nc;            // nc = ceil(D / 32) chunks, at most the instantiated NC
+  int record_bytes, canon_bytes, global;
+  const uint32_t *dtab;
+  float *out;
+};
+struct __attribute__((packed, aligned(1))) U32x4u {
+  uint32_t x, y, z, w;
+};
+struct __attribute__((packed, aligned(1))) U32u {
+  uint32_t v;
+};
+struct __attribute__((packed, aligned(1))) U16su {
+  uint16_t v;
+};
+constexpr int kScoreThreads = 512;
+
+template <int BITS, int NC>
+__global__ void __launch_bounds__(kScoreThreads, NC <= (BITS == 4 ? 8 : 16) ? 4 : 2) k_score_mfma(ScoreArgs a) {
+  using T = DecodeTab<BITS, NC>;
+  __shared__ __align__(16) uint32_t dtab[T::kEntries * T::kCopies * T::kWords];
+  constexpr int W = ((NC * BITS + 15) / 16) * 4;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t lane4 = uint32_t(lane) * 4u;
+  const int m = lane & 15, kq = lane >> 4;
+  // A rows, query 4 blockIdx.y + m / 4, part m % 4: 128 threads split a query
+  // into three float16 rows in the table's space, from which every lane reads
+  // its chunks
+  constexpr int kQLen = 32 * NC;
+  constexpr bool kFits = 12 * kQLen * 2 <= int(sizeof(dtab));
+  __shared__ __align__(16) _Float16 qown[kFits ? 8 : 12 * kQLen];
+  _Float16 *qs = kFits ? reinterpret_cast<_Float16 *>(dtab) : qown;
+  __shared__ float red_m[8];
+  __shared__ int red_f[8];
+  __shared__ float qscale[4];
+  {
+    const int q = 4 * blockIdx.y + (tid >> 7), t = tid & 127;
+    const float *qr = a.q_rot + int64_t(min(q, a.Q - 1)) * a.D;
+    float v[(kQLen + 127) / 128];
+    float mx = 0.f;
+    int fin = 1;
+#pragma unroll
+    for (int u = 0; u < (kQLen + 127) / 128; ++u) {
+      const int k = t + 128 * u;
+      v[u] = qr[min(k, a.D - 1)];
+      if (k >= a.D || q >= a.Q) v[u] = 0.f;
+      mx = fmaxf(mx, fabsf(v[u]));
+      fin &= fabsf(v[u]) < __builtin_inff() ? 1 : 0;
+    }
+    mx = wave_max(mx);
+    fin = __all(fin) ? 1 : 0;
+    if (lane == 0) {
+      red_m[wave] = mx;
+      red_f[wave] = fin;
+    }
+    __syncthreads();
+    mx = fmaxf(red_m[wave & ~1], red_m[wave | 1]);
+    fin = red_f[wave & ~1] & red_f[wave | 1];
+    const float scale = (fin && mx > 0.f) ? ldexpf(1.f, max(-126, min(126, 14 - ilogbf(mx)))) : 1.f;
+    if (t == 0) qscale[tid >> 7] = scale;
+    _Float16 *row = qs + (tid >> 7) * 3 * kQLen;
+#pragma unroll
+    for (int u = 0; u < (kQLen + 127) / 128; ++u) {
+      const int k = t + 128 * u;
+      // a query with an infinity or NaN: those coordinates alone decide
+      float x = fin ? v[u] * scale : (fabsf(v[u]) < __builtin_inff() ? 0.f : v[u]);
+      if (k < kQLen) {
+#pragma unroll
+        for (int part = 0; part < 3; ++part) {
+          const _Float16 h = static_cast<_Float16>(x);
+          row[part * kQLen + k] = h;
+          x = fin ? x - static_cast<float>(h) : 0.f;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  half8 av[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    half8 z = {};
+    if (c < a.nc && (m & 3) < 3)
+      z = *reinterpret_cast<const half8 *>(qs + ((m >> 2) * 3 + (m & 3)) * kQLen + kq * 8 * a.nc + 8 * c);
+    av[c] = z;
+  }
+  __syncthreads();   // the table is filled over the query rows
+#pragma unroll 16
+  for (int idx = tid; idx < T::kEntries * T::kCopies; idx += kScoreThreads) {
+    const int e = idx / T::kCopies;
+    if constexpr (T::kByte) {
+      constexpr int cw = T::kCompactWords;
+#pragma unroll
+      for (int w = 0; w < cw; ++w) {
+        dtab[idx * T::kWords + w] = a.dtab[(e & 15) * cw + w];
+        dtab[idx * T::kWords + cw + w] = a.dtab[(e >> 4) * cw + w];
+      }
+    } else {
+#pragma unroll
+      for (int w = 0; w < T::kWords; ++w) dtab[idx * T::kWords + w] = a.dtab[e * T::kWords + w];
+    }
+  }
+  // the query whose scores this lane writes is 4 blockIdx.y + kq; its scale
+  const float inv = 1.f / qscale[kq];
+  const int qo = 4 * blockIdx.y + kq;
+  float *out = a.out + int64_t(min(qo, a.Q - 1)) * a.n;
+  __syncthreads();
+
+  const int nb = a.nc * BITS;             // bytes of a lane's quarter
+  const int boff = kq * nb;
+  const int64_t n_tiles = (a.n + 15) / 16, step = int64_t(gridDim.x) * (kScoreThreads / 64);
+  // record of this lane in tile t: its words and scales (bits past the codes
+  // decode to some centroid and meet zero query coordinates)
+  auto load = [&](int64_t t, uint32_t (&w)[W], uint32_t &sc, bool &valid) {
+    const int64_t j = t * 16 + m;
+    int64_t r = -1;
+    if (j < a.n) r = a.ids ? a.ids[j] : j;
+    valid = r >= 0 && r < a.n_pool;
+    const int64_t at = (valid ? r : 0) * a.record_bytes;
+    const uint8_t *rec = a.records + at;
+    sc = reinterpret_cast<const U16su *>(rec + a.canon_bytes)->v;
+    sc |= (a.global ? uint32_t(reinterpret_cast<const U16su *>(rec + a.canon_bytes + 2)->v) : 0x7000u) << 16;
+    if (at + boff + ((nb + 3) & ~3) <= a.pool_bytes) {
+#pragma unroll
+      for (int u = 0; u < W / 4; ++u) {
+        if (16 * u + 16 <= nb) {   // uniform
+          const U32x4u v = *reinterpret_cast<const U32x4u *>(rec + boff + 16 * u);
+          w[4 * u] = v.x;
+          w[4 * u + 1] = v.y;
+          w[4 * u + 2] = v.z;
+          w[4 * u + 3] = v.w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            w[4 * u + e] = 16 * u + 4 * e < nb
+                               ? reinterpret_cast<const U32u *>(rec + boff + 16 * u + 4 * e)->v
+                               : 0u;
+        }
+      }
+    } else {   // the pool ends within the reads of its last records
+#pragma unroll
+      for (int e = 0; e < W; ++e) {
+        uint32_t v = 0u;
+#pragma unroll 1
+        for (int b = 0; b < 4; ++b)
+          if (4 * e + b < nb && at + boff + 4 * e + b < a.pool_bytes)
+            v |= uint32_t(rec[boff + 4 * e + b]) << (8 * b);
+        w[e] = v;
+      }
+    }
+  };
+  auto score = [&](int64_t t, const uint32_t (&w)[W], uint32_t sc, bool valid) {
+    floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+    half8 b[3];
+    b[0] = decode_chunk<BITS, NC>(dtab, w, 0, lane4);
+    if (NC > 1) b[1] = decode_chunk<BITS, NC>(dtab, w, NC > 1 ? 1 : 0, lane4);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if (c + 2 < NC) b[(c + 2) % 3] = decode_chunk<BITS, NC>(dtab, w, c + 2 < NC ? c + 2 : 0, lane4);
+      if (c & 1) acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[c], b[c % 3], acc1, 0, 0, 0);
+      else acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[c], b[c % 3], acc0, 0, 0, 0);
+    }
+    // lane (kq, m): rows 4 kq + {0, 1, 2}, the parts of query kq, of record m
+    const float dot = ((acc0[0] + acc1[0]) + ((acc0[1] + acc1[1]) + (acc0[2] + acc1[2]))) * inv;
+    const int64_t j = t * 16 + m;
+    if (j < a.n && qo < a.Q)
+      out[j] = valid ? dec_ue4m12(sc >> 16) * (dec_ue7m9(sc & 0xffffu) * dot) : -__builtin_inff();
+  };
+  uint32_t wa[W], sa = 0u;
+  bool va = false;
+  int64_t t = int64_t(blockIdx.x) * (kScoreThreads / 64) + wave;
+  if constexpr (W + 4 * NC > 150) {   // no registers for a second tile
+    for (; t < n_tiles; t += step) {
+      load(t, wa, sa, va);
+      score(t, wa, sa, va);
+    }
+    return;
+  }
+  uint32_t wb[W], sb = 0u;
+  bool vb = false;
+  if (t < n_tiles) load(t, wa, sa, va);
+  while (t < n_tiles) {   // the next tile's records are in flight while one is scored
+    if (t + step < n_tiles) load(t + step, wb, sb, vb);
+    score(t, wa, sa, va);
+    t += step;
+    if (t >= n_tiles) break;
+    if (t + step < n_tiles) load(t + step, wa, sa, va);
+    score(t, wb, sb, vb);
+    t += step;
+  }
+}
+
 // Profiling hook: events that take the start and end times of the scan
 // kernel's (0) and the top-k kernel's (1) own dispatch in later
 // rslm_scan_topk calls made by the same host thread (the setting is per
@@ -1330,6 +1542,43 @@ static void launch_scan_bits(int nc, bool multi, dim3 grid, hipStream_t s, const
   }
 #undef RSLM_SCAN_MP
 #undef RSLM_SCAN_NC
+}
+
+template <int BITS>
+static void launch_score_bits(const ScoreArgs &a, dim3 grid, hipStream_t s) {
+#define RSLM_SCORE_NC(NCV) \
+  hipLaunchKernelGGL((k_score_mfma<BITS, NCV>), grid, dim3(kScoreThreads), 0, s, a)
+  if (a.nc <= 2) RSLM_SCORE_NC(2);
+  else if (a.nc <= 4) RSLM_SCORE_NC(4);
+  else if (a.nc <= 6) RSLM_SCORE_NC(6);
+  else if (a.nc <= 8) RSLM_SCORE_NC(8);
+  else if (a.nc <= 12) RSLM_SCORE_NC(12);
+  else if (a.nc <= 16) RSLM_SCORE_NC(16);
+  else if (a.nc <= 24) RSLM_SCORE_NC(24);
+  else RSLM_SCORE_NC(32);
+#undef RSLM_SCORE_NC
+}
+
+bool launch_score_mfma(const rslm_plan *p, const uint8_t *records, int64_t n_pool, const int64_t *ids,
+                       int64_t n, const float *q_rot, int Q, float *out, hipStream_t s) {
+  const CodecParams &cp = p->codec;
+  if (cp.lead > 0 || cp.D > 1024) return false;
+  // from about 4,096 records on the table fill is paid for (us, k_score_reg
+  // against this: 5,000 of D = 300, 3 bits 20, 9; of D = 1,000, 1 bit 25, 15; 100,000
+  // of D = 128, 4 bits 14, 9)
+  if (n * ((Q + 3) / 4) < 4096) return false;
+  ScoreArgs a{records, n_pool * cp.record_bytes, n_pool, ids, n, q_rot, Q, cp.D, (cp.D + 31) / 32,
+              cp.record_bytes, cp.canon_bytes, cp.global, p->d_dtab, out};
+  const int64_t tiles = (n + 15) / 16, wgs = (tiles + kScoreThreads / 64 - 1) / (kScoreThreads / 64);
+  const int gy = (Q + 3) / 4;
+  const dim3 grid(unsigned(std::min<int64_t>(wgs, std::max(1, cu_count() * 2 / gy))), unsigned(gy));
+  switch (cp.bits) {
+    case 4: launch_score_bits<4>(a, grid, s); break;
+    case 3: launch_score_bits<3>(a, grid, s); break;
+    case 2: launch_score_bits<2>(a, grid, s); break;
+    default: launch_score_bits<1>(a, grid, s);
+  }
+  return true;
 }
 
 }  // namespace rslm
