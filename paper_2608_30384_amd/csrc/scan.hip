@@ -1168,7 +1168,17 @@ __global__ void __launch_bounds__(kStreamThreads) k_topk_stream(
   if (tid == 0) sm.overflow = 0;
   // the first kStreamCap scores are all candidates
   const int n0 = min(n, kStreamCap);
-  for (int i = tid; i < n0; i += nt) sm.buf[0][i] = (uint64_t(order_key(row[i])) << 32) | uint32_t(i);
+  if (n0 > 0) {   // every load before the stores
+    constexpr int kFirst = kStreamCap / kStreamThreads;
+    float v[kFirst];
+#pragma unroll
+    for (int u = 0; u < kFirst; ++u) v[u] = row[min(tid + kStreamThreads * u, n0 - 1)];
+#pragma unroll
+    for (int u = 0; u < kFirst; ++u) {
+      const int i = tid + kStreamThreads * u;
+      if (i < n0) sm.buf[0][i] = (uint64_t(order_key(v[u])) << 32) | uint32_t(i);
+    }
+  }
   __syncthreads();
   int cur = 0, cnt = n0;
   uint32_t T = 0;

@@ -130,23 +130,31 @@ __device__ __forceinline__ void for_each_key(const float *__restrict__ vals, int
 
 // Sorts the collected survivors and writes the k best (padding when fewer).
 // The k best of buf[0..cnt) (cnt <= blockDim.x, composites as above) in
-// (score desc, id asc) order, (-inf, -1) padded: one entry per thread, whose
-// rank is the number of entries ahead of it (equal composites ordered by
-// slot).  One pass instead of a sort's barrier-separated stages.
+// (score desc, id asc) order, (-inf, -1) padded.  An entry's rank is the number
+// of entries ahead of it (equal composites ordered by slot): one pass instead
+// of a sort's barrier-separated stages, a chain of LDS reads as long as the
+// entries each thread compares, so a small set is shared out over the threads.
 __device__ __forceinline__ void rank_emit(const uint64_t *buf, int cnt, int k,
                                           float *__restrict__ out_s, int32_t *__restrict__ out_i) {
   const int t = threadIdx.x;
-  if (t < cnt) {
-    const uint64_t e = buf[t];
-    int r = 0;
-    for (int j = 0; j < cnt; ++j) {
+  // share 2^lp adjacent lanes per candidate, as many as the workgroup has (at
+  // most 16): each counts every 2^lp-th entry
+  int lp = 0;
+  while (lp < 4 && (cnt << (lp + 1)) <= int(blockDim.x)) ++lp;
+  const int c = t >> lp, share = t & ((1 << lp) - 1);
+  const uint64_t e = buf[min(c, max(cnt - 1, 0))];
+  int r = 0;
+  if (c < cnt) {
+#pragma unroll 4
+    for (int j = share; j < cnt; j += 1 << lp) {
       const uint64_t v = buf[j];
-      r += (v > e) || (v == e && j < t);
+      r += (v > e) || (v == e && j < c);
     }
-    if (r < k) {
-      out_s[r] = key_to_float(uint32_t(e >> 32));
-      out_i[r] = int32_t(0xffffffffu - uint32_t(e & 0xffffffffu));
-    }
+  }
+  for (int off = 1; off < (1 << lp); off <<= 1) r += __shfl_xor(r, off, 64);
+  if (c < cnt && share == 0 && r < k) {
+    out_s[r] = key_to_float(uint32_t(e >> 32));
+    out_i[r] = int32_t(0xffffffffu - uint32_t(e & 0xffffffffu));
   }
   for (int j = cnt + t; j < k; j += blockDim.x) {
     out_s[j] = -__builtin_inff();
