@@ -46,7 +46,7 @@ struct __attribute__((packed, aligned(1))) U64u {
 // vector) ran three.  Whole calls, us, against one row per vector for D = 128
 // NB and 1-D codebooks, and a vector in LDS for the rest: 65,536 x 768 4-bit +
 // SQ8 171 -> 123; 524,288 x 768 two-stage 1,314 -> 998; 65,536 x 1,024 2-bit 816
-// -> 150; 65,536 x 2,049 4-bit with packed records 1,423 -> 375; 153,633 x 698
+// -> 150; 65,536 x 2,049 4-bit 1,307 -> 288 (kernel); 153,633 x 698
 // two-stage 1,425 -> 395.  At D = 128 and 256 with 1-D codebooks (one row
 // either way): 1,000,000 x 128 194 -> 180, 700,000 x 256 295 -> 271, but calls of
 // 12 to 18 us take about 1 us longer (30,000 x 128: 12.0 -> 13.0).

@@ -134,6 +134,8 @@ __device__ __forceinline__ void for_each_key(const float *__restrict__ vals, int
 // of entries ahead of it (equal composites ordered by slot): one pass instead
 // of a sort's barrier-separated stages, a chain of LDS reads as long as the
 // entries each thread compares, so a small set is shared out over the threads.
+// Kernels that end with it, us, one thread per entry against this: top-k of 256
+// queries at 1,000,000 x 96 22.9, 21.2; SQ8 rescoring of 100 candidates 7.8, 6.6.
 __device__ __forceinline__ void rank_emit(const uint64_t *buf, int cnt, int k,
                                           float *__restrict__ out_s, int32_t *__restrict__ out_i) {
   const int t = threadIdx.x;
