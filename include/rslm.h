@@ -272,9 +272,15 @@ int rslm_score(const rslm_plan *plan, const uint8_t *records, int64_t n_pool,
  *                  n x nprobe (out_scores = the dots).
  *   x: n x dim, centroids: nlist x dim (float32).  nlist <= 65536,
  *   nprobe <= min(nlist, 1024).
- *   Large IVF_ASSIGN_L2 calls keep the centres' float16 halves in the
- *   workspace; one of 4 nlist bytes (rounded to 256) is accepted as well and
- *   takes the float32 kernels.
+ *   Large IVF_ASSIGN_L2 calls (at least 128 rows of 16 to 16,384 coordinates,
+ *   and centres enough) sort the centres out on float16 halves of both
+ *   operands and settle what is close in float64: the centre nearest in
+ *   float64, and a distance rounded to float32 once.  They ask for at most 64
+ *   MiB and give the same results with any workspace that they run in: as much
+ *   as asked for, or less, down to pieces of 4,096 rows.  One too small for
+ *   that, or not 16-byte aligned, is accepted from 4 nlist bytes (rounded to
+ *   256) on and takes the float32 kernels of smaller calls, whose sums are
+ *   rounded in float32.
  * ------------------------------------------------------------------------ */
 #define IVF_ASSIGN_L2 0
 #define IVF_PROBE_IP 1
@@ -294,8 +300,9 @@ int ivf_assign_probe(const float *x, int64_t n, int32_t dim,
  * holds once per GPU it runs on until the process ends.  This call allocates
  * nothing (no hipMalloc / hipFree, no allocating library routine); the
  * caller passes inputs and outputs as for ivf_assign_probe.
- *   Sizes whose least workspace exceeds the limit -- probing needs n * nlist *
- *   4 bytes plus 4 * nlist rounded to 256, assignment the latter -- return
+ *   Large assignments go through it piece by piece, with the results of
+ *   ivf_assign_probe.  Sizes whose least workspace exceeds the limit -- probing
+ *   needs n * nlist * 4 bytes plus 4 * nlist rounded to 256 -- return
  *   RSLM_ERR_WORKSPACE before any launch.
  *   Every call on one GPU shares that GPU's scratch: calls that overlap in
  *   time on one GPU (different streams, threads or processes' graphs) race

@@ -9,6 +9,7 @@
 // running (distance, id) minimum per row across all centre tiles (128 x 128
 // output tiles), never writing the product; rows that are not whole 16-byte
 // runs take a vector-ALU tile (64 x 64, 4 x 4 outputs per thread) instead.
+#include <algorithm>
 #include <mutex>
 
 #include "rslm_internal.h"
@@ -399,13 +400,17 @@ __global__ void __launch_bounds__(256) k_assign_mfma(const float *__restrict__ x
 // float16 halves, v s = hi + lo with s a power of two per row that puts the
 // row's largest magnitude in [2^14, 2^15), and <x, c> is accumulated in
 // float32 as hi hi + hi lo + lo hi on v_mfma_f32_16x16x32_f16 (16 times the
-// float32 rate per product).  hi + lo carries 22 to 23 significant bits (and
-// never less than 2^-39 of the row's largest element); what is dropped, lo lo,
-// is below 2^-22 of each product.  Both are smaller than the roundings of the
-// float32 sum, which has D / 32 steps here against D / 4 there.  Error of the
-// distances against float64 (2-norm, relative): 524,288 x 768 by 4,096 1.7e-7,
-// float32 kernel 8.9e-7; 100,000 x 1,447 by 3,000 2.2e-7 and 1.5e-6; 524,288 x
-// 100 by 4,096 1.5e-7 and 4.7e-7.
+// float32 rate per product).  These products only sort the centres out: with
+// every value goes a bound t(x, c) of its distance from the exact
+// ||c||^2 - 2 <x, c> (split_margin), a row whose best value beats every other
+// one by more than the bounds is decided, and the rows that are left (near
+// ties, rows with one coordinate far above the rest, infinities and NaN) are
+// evaluated against every centre in float64 (k_assign_exact).  The centre
+// returned is thus the nearest one in float64, the lowest id where two are
+// equal there, at any D and whatever the values' spread, and the distance is a
+// float64 sum rounded once.  A pair's product does not depend on the other
+// rows and centres of its tile, so results do not depend on how a call is cut
+// into shares, groups and pieces, that is, on the workspace.
 //
 // A workgroup of eight wavefronts owns 256 rows of x and walks its share of
 // the centres in tiles of 256: with both sides at 256 each operand is read
@@ -414,17 +419,13 @@ __global__ void __launch_bounds__(256) k_assign_mfma(const float *__restrict__ x
 // of x as they are staged (they are too many to keep).  k goes through LDS in
 // slabs of 32, two buffers, one barrier per slab.  Centres are the M side, so
 // a lane holds 32 centres of each of four rows and keeps four running minima.
-// 1,048,576 x 768 by 4,096: 52.6 ms on the float32 kernel, 20.2 ms here (327
-// TFLOP/s of distances, 981 TFLOP/s of float16 products; a large bf16 library
-// product runs at 1,370 on the same card).  The same tiles with the centres
-// staged through registers 30.6 ms, with two slabs of both operands in
-// registers 38.8 ms (spills).
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 constexpr int kSpM = 256, kSpN = 256, kSpK = 32, kSpThreads = 512;
 constexpr int kSpRow = 4 * kSpK;       // bytes per LDS row: hi, then lo
 constexpr int kWaitVm0 = 0x0F70;       // s_waitcnt vmcnt(0), the other counters free
-constexpr int kSlowRow = int(0x80000000);   // id of a row left to k_assign_finish
+constexpr float kFarthest = 3.4e38f;   // values from here on are not chosen
+constexpr int32_t kNoCentre = 0x7fffffff;
 
 struct __attribute__((packed, aligned(4))) F4u {
   float x, y, z, w;
@@ -437,15 +438,48 @@ __device__ __forceinline__ float split_scale(float m) {
   return ldexpf(1.f, max(-126, min(126, 14 - ilogbf(m))));
 }
 
-// One wavefront per centre (nlist rounded up to whole tiles): ||c||^2 (summed
-// in float64; +inf past nlist, so padding is never nearest), -2 / s, and the
-// halves, slab by slab (32 hi, then 32 lo, zero past D).
+// What is kept of a centre besides its halves.
+struct CentreTab {
+  float *base;     // ||c||^2 less the margin's part without x; +inf where ||c||^2
+                   // is not finite and past nlist: never nearest
+  float *along;    // the margin's factor of ||x||
+  float *margin;   // the margin's part without x
+  float *mul;      // -2 / s
+  double *norm;    // ||c||^2; +inf as above
+};
+
+// t(x, c) = margin + along ||x|| bounds the difference of the computed value
+// fma(acc mul, 1 / s_x, ||c||^2) from the exact one, in units u = 2^-24 of
+// ||x|| ||c||:
+//   operands   what hi + lo leaves out is at most 2^-22 of a coordinate (and
+//              2^-25 of the scaled row's unit where lo is subnormal; 2^-14 were
+//              subnormal halves read as 0), and lo lo is dropped: 3 2^-22 of
+//              every product, and 2 sqrt(D) 2^-28 of the whole, at most 16 u for D
+//              <= 16,384                                               12 + 16
+//   products   32 exact products per instruction: at most 34 roundings or
+//              truncations of 2^-23 of their absolute sum                   68
+//   slabs      one float32 addition each                                D / 32
+// twice that, since 2 <x, c> is taken, is 192 + D / 16; 16 more for the
+// roundings of the norms and of the value itself, which also take 8 u of
+// ||c||^2.  2^-100 and 1e-30 cover scales that were clamped and underflow.
+constexpr int kSplitMaxDim = 16384;
+__device__ __forceinline__ void split_margin(int D, float cnorm, float &along, float &margin) {
+  const float u = 0x1p-24f;
+  along = u * (208.f + D / 16.f) * (sqrtf(cnorm) * 1.001f + 0x1p-100f);
+  margin = u * 8.f * cnorm + 1e-30f;
+}
+
+// One wavefront per centre (nlist rounded up to whole tiles): its table
+// entries, and the halves of those of the tiles [t0, t1), slab by slab (32 hi,
+// then 32 lo, zero past D).  Workgroup 0 also clears the list's length.
 __global__ void __launch_bounds__(256) k_split_centres(const float *__restrict__ cen, int nlist, int D,
-                                                       int n_slab, float *__restrict__ cnorm,
-                                                       float *__restrict__ cmul,
-                                                       _Float16 *__restrict__ split) {
+                                                       int n_slab, int c0, CentreTab tab,
+                                                       _Float16 *__restrict__ split,
+                                                       int32_t *__restrict__ n_listed) {
   const int lane = threadIdx.x & 63;
-  const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int cg = blockIdx.x * 4 + (threadIdx.x >> 6);   // within the group
+  const int c = c0 + cg;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *n_listed = 0;
   const float *row = cen + int64_t(c) * D;
   const bool in = c < nlist;
   double sum = 0.0;
@@ -457,52 +491,90 @@ __global__ void __launch_bounds__(256) k_split_centres(const float *__restrict__
   }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  const float sc = split_scale(wave_max(m));
+  const float cn = float(sum);
+  const bool ok = in && cn < __builtin_inff();   // (not for a NaN)
+  const float sc = split_scale(wave_max(ok ? m : 0.f));
   if (lane == 0) {
-    cnorm[c] = in ? float(sum) : __builtin_inff();
-    cmul[c] = -2.f / sc;
+    float along = 0.f, margin = 0.f;
+    if (ok) split_margin(D, cn, along, margin);
+    tab.base[c] = ok ? cn - margin : __builtin_inff();
+    tab.along[c] = along;
+    tab.margin[c] = margin;
+    tab.mul[c] = -2.f / sc;
+    tab.norm[c] = ok ? sum : double(__builtin_inff());
   }
-  _Float16 *out = split + int64_t(c) * n_slab * (2 * kSpK);
+  _Float16 *out = split + int64_t(cg) * n_slab * (2 * kSpK);
   for (int i = lane; i < n_slab * kSpK; i += 64) {
-    const float v = (in && i < D) ? row[i] * sc : 0.f;
+    const float v = (ok && i < D) ? row[i] * sc : 0.f;
     const _Float16 h = static_cast<_Float16>(v);
     out[(i / kSpK) * (2 * kSpK) + i % kSpK] = h;
     out[(i / kSpK) * (2 * kSpK) + kSpK + i % kSpK] = static_cast<_Float16>(v - static_cast<float>(h));
   }
 }
 
-// Workgroup (rows, share): nearest of the centres [tiles t0, t1) of 256 for
-// 256 rows; (distance without ||x||^2, id) to best_v / best_i at [share][row].
+// What a share of the centres leaves of a row: the lowest lower bound w = value
+// - t, its centre, and the second lowest w.
+struct SplitPart {
+  float *w1, *w2;
+  int32_t *id;
+};
+
+// Takes (w1, id, w2) of disjoint sets of centres together.
+__device__ __forceinline__ void merge_part(float &w1, int32_t &id, float &w2, float ow1, int32_t oid,
+                                           float ow2) {
+  w2 = fminf(fminf(w2, ow2), fmaxf(w1, ow1));
+  if (ow1 < w1 || (ow1 == w1 && oid < id)) {
+    w1 = ow1;
+    id = oid;
+  }
+}
+
+// Workgroup (rows, share): its share of the tiles [0, n_tiles) of 256 centres
+// at `split` (of which the first is centre c0) for 256 of the rows of x, to
+// `part` at [share][row], and ||x|| to xnorm.  Whole call, 1,048,576 x 768 by
+// 4,096: 52.5 ms on the float32 kernel, 20.4 ms here (324 TFLOP/s of distances,
+// 970 TFLOP/s of float16 products; a large bf16 library product runs at 1,370 on
+// the same card).  The same tiles with the centres staged through registers took
+// 10 ms more, with two slabs of both operands in registers 18 ms (spills).
 __global__ void __launch_bounds__(kSpThreads, 2) k_assign_split(
-    const float *__restrict__ x, int64_t n, int D, int n_slab, const float *__restrict__ cnorm,
-    const float *__restrict__ cmul, const _Float16 *__restrict__ split, int n_tiles,
-    int tiles_per_share, float *__restrict__ best_v, int32_t *__restrict__ best_i) {
+    const float *__restrict__ x, int64_t n, int D, int n_slab, int c0, CentreTab tab,
+    const _Float16 *__restrict__ split, int n_tiles, int tiles_per_share, SplitPart part,
+    float *__restrict__ xnorm) {
   // rows of 128 bytes (32 hi, 32 lo): x, then centres; the eight 16-byte units
   // of row r are stored at unit ^ (r % 8), which spreads a column of units
   // over the banks without padding (the centres are written by lanes in order)
   __shared__ __align__(128) uint8_t lds[2][(kSpM + kSpN) * kSpRow];
-  __shared__ float xscale[kSpM];
+  __shared__ float xscale[kSpM], xlen[kSpM];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 15, h = lane >> 4;
   const int wx = (wave & 3) * 64, wc = (wave >> 2) * 128;   // this wave's rows and centres
   const int64_t r0 = int64_t(blockIdx.x) * kSpM;
   const int t0 = blockIdx.y * tiles_per_share, t1 = min(n_tiles, t0 + tiles_per_share);
-  // largest magnitude of each row: 32 rows per wavefront, four in flight
+  // largest magnitude and length of each row: 32 rows per wavefront, four in
+  // flight.  A row with an infinity or a NaN, or whose ||x||^2 overflows, gets a
+  // length of +inf or NaN, with which no value is decided.
   for (int q = 0; q < 32; q += 4) {
-    float mx[4] = {0.f, 0.f, 0.f, 0.f};
+    float mx[4] = {0.f, 0.f, 0.f, 0.f}, ss[4] = {0.f, 0.f, 0.f, 0.f};
     for (int k = lane; k < D; k += 64) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int64_t r = min(r0 + wave * 32 + q + u, n - 1);
-        mx[u] = fmaxf(mx[u], fabsf(x[r * D + k]));
+        const float v = x[r * D + k];
+        mx[u] = fmaxf(mx[u], fabsf(v));
+        ss[u] = fmaf(v, v, ss[u]);
       }
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       mx[u] = wave_max(mx[u]);
-      // an infinite row is marked (by a zero scale) and left to k_assign_finish
-      if (lane == 0) xscale[wave * 32 + q + u] = mx[u] < __builtin_inff() ? split_scale(mx[u]) : 0.f;
+      ss[u] = wave_sum(ss[u]);
+      const int rl = wave * 32 + q + u;
+      if (lane == 0) {
+        xscale[rl] = split_scale(mx[u]);
+        xlen[rl] = sqrtf(ss[u]);
+        if (blockIdx.y == 0 && r0 + rl < n) xnorm[r0 + rl] = sqrtf(ss[u]);
+      }
     }
   }
   __syncthreads();
@@ -563,14 +635,14 @@ __global__ void __launch_bounds__(kSpThreads, 2) k_assign_split(
           16, 0, 0);
   };
   floatx4_t acc[8][4];
-  float best[4], inv[4];
+  float best[4], second[4], inv[4], len[4];
   int32_t bid[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    best[j] = 3.4e38f;
-    bid[j] = 0x7fffffff;
-    const float s = xscale[wx + 16 * j + m];
-    inv[j] = s > 0.f ? 1.f / s : 0.f;
+    best[j] = second[j] = __builtin_inff();
+    bid[j] = kNoCentre;
+    inv[j] = 1.f / xscale[wx + 16 * j + m];
+    len[j] = xlen[wx + 16 * j + m];
   }
   // Slabs in one sequence over the tiles.  While slab s is multiplied, the
   // centres of slab s + 1 go to LDS, the coordinates of x of slab s + 1 (loaded
@@ -624,21 +696,26 @@ __global__ void __launch_bounds__(kSpThreads, 2) k_assign_split(
       for (int j = 0; j < 4; ++j) acc[i][j] += t[j];
     }
     if (last) {
-      // lane (m, h) holds centres c0 + wc + 16 i + 4 h + e of rows wx + 16 j + m
-      const int c0 = tile * kSpN + wc + 4 * h;
+      // lane (m, h) holds centres c + 16 i + 4 h + e of rows wx + 16 j + m
+      const int c = c0 + tile * kSpN + wc + 4 * h;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float4 cn = *reinterpret_cast<const float4 *>(cnorm + c0 + 16 * i);
-        const float4 cm = *reinterpret_cast<const float4 *>(cmul + c0 + 16 * i);
-        const float cna[4] = {cn.x, cn.y, cn.z, cn.w}, cma[4] = {cm.x, cm.y, cm.z, cm.w};
+        const float4 cb = *reinterpret_cast<const float4 *>(tab.base + c + 16 * i);
+        const float4 ca = *reinterpret_cast<const float4 *>(tab.along + c + 16 * i);
+        const float4 cm = *reinterpret_cast<const float4 *>(tab.mul + c + 16 * i);
+        const float cba[4] = {cb.x, cb.y, cb.z, cb.w}, caa[4] = {ca.x, ca.y, ca.z, ca.w},
+                    cma[4] = {cm.x, cm.y, cm.z, cm.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const float v = fmaf(acc[i][j][e], cma[e] * inv[j], cna[e]);   // ||c||^2 - 2 <x, c>
-            if (v < best[j]) {   // centres visited in increasing order
-              best[j] = v;
-              bid[j] = c0 + 16 * i + e;
+            // ||c||^2 - 2 <x, c> - t (the scales one after the other: their
+            // product can underflow where the value does not)
+            const float w = fmaf(acc[i][j][e] * cma[e], inv[j], fmaf(-caa[e], len[j], cba[e]));
+            second[j] = __builtin_amdgcn_fmed3f(best[j], second[j], w);   // of three, as best <= second
+            if (w < best[j]) {   // centres visited in increasing order
+              best[j] = w;
+              bid[j] = c + 16 * i + e;
             }
           }
       }
@@ -650,26 +727,23 @@ __global__ void __launch_bounds__(kSpThreads, 2) k_assign_split(
     __builtin_amdgcn_s_waitcnt(kWaitVm0);   // the centres are in LDS
     __syncthreads();
   }
-  // merge the four lanes and the two wavefronts holding a row: lexicographic
-  // (value, id)
+  // merge the four lanes and the two wavefronts holding a row
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int off = 16; off < 64; off <<= 1) {
-      const float ov = __shfl_xor(best[j], off, 64);
-      const int oi = __shfl_xor(bid[j], off, 64);
-      if (ov < best[j] || (ov == best[j] && oi < bid[j])) {
-        best[j] = ov;
-        bid[j] = oi;
-      }
-    }
+    for (int off = 16; off < 64; off <<= 1)
+      merge_part(best[j], bid[j], second[j], __shfl_xor(best[j], off, 64), __shfl_xor(bid[j], off, 64),
+                 __shfl_xor(second[j], off, 64));
   float *red_v = reinterpret_cast<float *>(lds[0]);   // the last slab was multiplied before a barrier
-  int32_t *red_i = reinterpret_cast<int32_t *>(red_v + kSpM);
+  float *red_s = red_v + kSpM;
+  int32_t *red_i = reinterpret_cast<int32_t *>(red_s + kSpM);
   if (wave >= 4 && h == 0) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      red_v[wx + 16 * j + m] = best[j];
-      red_i[wx + 16 * j + m] = bid[j];
+      const int rl = wx + 16 * j + m;
+      red_v[rl] = best[j];
+      red_s[rl] = second[j];
+      red_i[rl] = bid[j];
     }
   }
   __syncthreads();
@@ -678,122 +752,372 @@ __global__ void __launch_bounds__(kSpThreads, 2) k_assign_split(
   for (int j = 0; j < 4; ++j) {
     const int rl = wx + 16 * j + m;
     if (r0 + rl >= n) continue;
-    if (red_v[rl] < best[j] || (red_v[rl] == best[j] && red_i[rl] < bid[j])) {
-      best[j] = red_v[rl];
-      bid[j] = red_i[rl];
-    }
+    merge_part(best[j], bid[j], second[j], red_v[rl], red_i[rl], red_s[rl]);
     const int64_t at = int64_t(blockIdx.y) * n + r0 + rl;
-    if (best_v) best_v[at] = best[j];
-    best_i[at] = inv[j] > 0.f ? bid[j] : kSlowRow;
+    part.w1[at] = best[j];
+    part.w2[at] = second[j];
+    part.id[at] = bid[j];
   }
 }
 
-// One wavefront per row: the best of the shares, and ||x||^2 + its value as
-// the distance.  A row with an infinite coordinate is compared with every
-// centre in float32.
-__global__ void __launch_bounds__(256) k_assign_finish(
-    const float *__restrict__ x, int64_t n, int D, const float *__restrict__ cen, int nlist,
-    const float *__restrict__ cnorm, int shares, const float *best_v, const int32_t *best_i,
-    int32_t *out_ids, float *out_d) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
+// One thread per row: the shares taken together; the centre where the row is
+// decided, else ~(its place in the list).
+__global__ void __launch_bounds__(256) k_assign_decide(int64_t n, int shares, SplitPart part,
+                                                       const float *__restrict__ xnorm, CentreTab tab,
+                                                       int32_t *__restrict__ list,
+                                                       int32_t *__restrict__ n_listed,
+                                                       int32_t *__restrict__ out_ids) {
+  const int64_t row = int64_t(blockIdx.x) * 256 + threadIdx.x;
   if (row >= n) return;
-  float v = __builtin_inff();
-  int32_t id = 0x7fffffff;
-  for (int s = lane; s < shares; s += 64) {
-    const float ov = best_v ? best_v[int64_t(s) * n + row] : 0.f;
-    const int32_t oi = best_i[int64_t(s) * n + row];
-    if (oi == kSlowRow || (id != kSlowRow && (ov < v || (ov == v && oi < id)))) {
-      v = ov;
-      id = oi;
-    }
+  float w1 = __builtin_inff(), w2 = __builtin_inff();
+  int32_t id = kNoCentre;
+  for (int s = 0; s < shares; ++s) {
+    const int64_t at = int64_t(s) * n + row;
+    merge_part(w1, id, w2, part.w1[at], part.id[at], part.w2[at]);
   }
-  for (int off = 1; off < 64; off <<= 1) {
-    const float ov = __shfl_xor(v, off, 64);
-    const int32_t oi = __shfl_xor(id, off, 64);
-    if (oi == kSlowRow || (id != kSlowRow && (ov < v || (ov == v && oi < id)))) {
-      v = ov;
-      id = oi;
-    }
+  bool decided = false;
+  if (id != kNoCentre) {
+    // w1 + 2 t is at least the exact value of the best
+    const float up = fmaf(2.f, fmaf(tab.along[id], xnorm[row], tab.margin[id]), w1);
+    decided = up < w2 && up < 1e37f;
   }
-  const float *xr = x + row * D;
-  if (id == kSlowRow) {
-    v = 3.4e38f;
-    id = 0x7fffffff;
-    for (int c = 0; c < nlist; ++c) {
-      float dot = 0.f;
-      for (int k = lane; k < D; k += 64) dot += xr[k] * cen[int64_t(c) * D + k];
-      dot = wave_sum(dot);
-      const float w = cnorm[c] - 2.f * dot;
-      if (w < v) {
-        v = w;
-        id = c;
+  if (decided) {
+    out_ids[row] = id;
+  } else {
+    const int32_t at = atomicAdd(n_listed, 1);
+    list[at] = int32_t(row);
+    out_ids[row] = ~at;
+  }
+}
+
+// The listed rows against every centre in float64: workgroups take (64 rows,
+// share of the centres) items, as many shares as fill the chip, so that a few
+// rows cost the time of one tile (us, no row listed against some: 1,024 x 256 by
+// 256 57, 82), which its chain of slabs sets.  Values are
+// ||c||^2 - 2 <x, c>; the lowest and its lowest id, kNoCentre where no value is
+// below 3.4e38 (and infinite and NaN products as in float32).
+constexpr int kExT = 64, kExK = 32, kExGrid = 1024;
+constexpr int kExParts = kExGrid * kExT;   // (row, share) results kept at a time
+__device__ __forceinline__ int exact_shares(int rows, int nlist) {
+  const int blocks = (rows + kExT - 1) / kExT;
+  return max(1, min(kExGrid / max(blocks, 1), (nlist + kExT - 1) / kExT));
+}
+__global__ void __launch_bounds__(256) k_assign_exact(const float *__restrict__ x, int D,
+                                                      const float *__restrict__ cen, int nlist,
+                                                      const double *__restrict__ norm,
+                                                      const int32_t *__restrict__ list,
+                                                      const int32_t *__restrict__ n_listed,
+                                                      double *__restrict__ part_v,
+                                                      int32_t *__restrict__ part_i,
+                                                      int32_t *__restrict__ out_ids) {
+  __shared__ double As[kExK][kExT], Bs[kExK][kExT];
+  const int rows = *n_listed;
+  const int blocks = (rows + kExT - 1) / kExT;
+  const int shares = exact_shares(rows, nlist);
+  const int tiles = (nlist + kExT - 1) / kExT, per = (tiles + shares - 1) / shares;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  const int lr = threadIdx.x & 63, lk = (threadIdx.x >> 6) * 8;   // staging: row, first k
+  for (int item = blockIdx.x; item < blocks * shares; item += gridDim.x) {
+    const int blk = item / shares, share = item - blk * shares;
+    const int64_t arow = int64_t(list[min(blk * kExT + lr, rows - 1)]) * D;
+    double best[4];
+    int32_t bid[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      best[i] = double(kFarthest);
+      bid[i] = kNoCentre;
+    }
+    for (int t = share * per; t < min(tiles, share * per + per); ++t) {
+      const int c0 = t * kExT;
+      const int64_t brow = int64_t(min(c0 + lr, nlist - 1)) * D;
+      double acc[4][4] = {};
+      float a[8], b[8];   // the next slab, on its way while one is multiplied
+      auto load = [&](int k0) {
+        if (k0 + kExK <= D) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const F4u u = *reinterpret_cast<const F4u *>(x + arow + k0 + lk + 4 * q);
+            const F4u v = *reinterpret_cast<const F4u *>(cen + brow + k0 + lk + 4 * q);
+            a[4 * q] = u.x, a[4 * q + 1] = u.y, a[4 * q + 2] = u.z, a[4 * q + 3] = u.w;
+            b[4 * q] = v.x, b[4 * q + 1] = v.y, b[4 * q + 2] = v.z, b[4 * q + 3] = v.w;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int k = k0 + lk + e;
+            a[e] = k < D ? x[arow + min(k, D - 1)] : 0.f;
+            b[e] = k < D ? cen[brow + min(k, D - 1)] : 0.f;
+          }
+        }
+      };
+      load(0);
+      for (int k0 = 0; k0 < D; k0 += kExK) {
+        __syncthreads();   // the previous slab is done with
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          As[lk + e][lr] = double(a[e]);
+          Bs[lk + e][lr] = double(b[e]);
+        }
+        __syncthreads();
+        if (k0 + kExK < D) load(k0 + kExK);
+#pragma unroll 4
+        for (int kk = 0; kk < kExK; ++kk) {
+          double av[4], bv[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) av[i] = As[kk][ty * 4 + i];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tx * 4 + j];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
+        }
       }
-    }
-  }
-  if (out_d) {
-    double s = 0.0;
-    for (int k = lane * 4; k < D; k += 256) {
-      if (k + 4 <= D) {
-        const F4u q = *reinterpret_cast<const F4u *>(xr + k);
-        s += double(q.x) * q.x + double(q.y) * q.y + (double(q.z) * q.z + double(q.w) * q.w);
-      } else {
-        for (int e = k; e < D; ++e) s += double(xr[e]) * xr[e];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int c = c0 + tx * 4 + j;
+        const double cn = c < nlist ? norm[c] : double(__builtin_inff());
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const double v = fma(-2.0, acc[i][j], cn);
+          if (v < best[i]) {   // centres visited in increasing order
+            best[i] = v;
+            bid[i] = c;
+          }
+        }
       }
     }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) out_d[row] = float(s + double(v));
+    for (int i = 0; i < 4; ++i)
+      for (int off = 8; off >= 1; off >>= 1) {
+        const double ov = __shfl_xor(best[i], off, 64);
+        const int32_t oi = __shfl_xor(bid[i], off, 64);
+        if (ov < best[i] || (ov == best[i] && oi < bid[i])) {
+          best[i] = ov;
+          bid[i] = oi;
+        }
+      }
+    if (tx == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int at = blk * kExT + ty * 4 + i;
+        if (at >= rows) continue;
+        if (shares == 1) {
+          out_ids[list[at]] = bid[i];
+        } else {   // blocks * shares <= kExGrid
+          part_v[share * (blocks * kExT) + at] = best[i];
+          part_i[share * (blocks * kExT) + at] = bid[i];
+        }
+      }
+    }
   }
-  if (lane == 0) out_ids[row] = id;
+}
+// The listed row at place `at`: its centre.
+__device__ __forceinline__ int32_t exact_id(int at, int rows, int nlist, const double *part_v,
+                                            const int32_t *part_i) {
+  const int stride = (rows + kExT - 1) / kExT * kExT, shares = exact_shares(rows, nlist);
+  double v = double(kFarthest);
+  int32_t id = kNoCentre;
+  for (int s = 0; s < shares; ++s) {
+    const double ov = part_v[s * stride + at];
+    const int32_t oi = part_i[s * stride + at];
+    if (ov < v || (ov == v && oi < id)) {
+      v = ov;
+      id = oi;
+    }
+  }
+  return id;
 }
 
-// Whether an assignment runs on split float16, and its workspace.
-struct SplitWs {
-  float *cnorm, *cmul;
-  _Float16 *split;
-  float *part_v;
-  int32_t *part_i;
-  int tiles, n_slab, shares, tiles_per_share;
-  size_t bytes;
-};
-static bool assign_on_split(int64_t n, int dim, int nlist) {
-  // Rows that are whole 16-byte runs have the float32 matrix kernel to beat:
-  // up to 128 centres half a tile of 256 or more is padding (us, float32
-  // against split: 65,536 x 512 by 128 113, 119; 1,011,082 x 922 by 188 18,536 on
-  // the vector ALU, 3,472), and below 128 rows there is too little work (64 x 768
-  // by 1,024 91, 104; 256 x 768 by 4,096 149, 105).  Other rows have a vector-ALU
-  // kernel, slower from a few microseconds of work on (4,573 x 230 by 21 87, 52;
-  // 20,000 x 1,501 by 16 1,114, 242).
-  if (dim % 4 == 0) return nlist > 128 && n >= 128;
-  return double(n) * double(nlist) * double(dim) >= 1e6;
+// Without distances: the listed rows' centres from their shares.
+__global__ void __launch_bounds__(256) k_assign_listed(const int32_t *__restrict__ list,
+                                                       const int32_t *__restrict__ n_listed, int nlist,
+                                                       const double *__restrict__ part_v,
+                                                       const int32_t *__restrict__ part_i,
+                                                       int32_t *__restrict__ out_ids) {
+  const int rows = *n_listed;
+  if (exact_shares(rows, nlist) == 1) return;   // already written
+  for (int at = blockIdx.x * 256 + threadIdx.x; at < rows; at += gridDim.x * 256)
+    out_ids[list[at]] = exact_id(at, rows, nlist, part_v, part_i);
 }
-static SplitWs assign_split_ws(void *base, int64_t n, int dim, int nlist) {
-  SplitWs w{};
-  char *p = static_cast<char *>(base);
+
+// With distances: one wavefront per row, the same, and ||x - c||^2 summed in
+// float64.  A row with an infinity has no finite distance (NaN, as inf - inf
+// in ||x||^2 + (||c||^2 - 2 <x, c>)); one without a centre gets ||x||^2 + 3.4e38.
+__global__ void __launch_bounds__(256) k_assign_finish(const float *__restrict__ x, int64_t n, int D,
+                                                       const float *__restrict__ cen, int nlist,
+                                                       const int32_t *__restrict__ n_listed,
+                                                       const double *__restrict__ part_v,
+                                                       const int32_t *__restrict__ part_i,
+                                                       int32_t *__restrict__ out_ids,
+                                                       float *__restrict__ out_d) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (row >= n) return;
+  int32_t id = out_ids[row];
+  if (id < 0) {
+    id = exact_id(~id, *n_listed, nlist, part_v, part_i);
+    if (lane == 0) out_ids[row] = id;
+  }
+  const bool has = id < nlist;
+  const float *xr = x + row * D;
+  const float *cr = cen + int64_t(has ? id : 0) * D;
+  double s = 0.0;
+  for (int k = lane * 4; k < D; k += 256) {
+    float v[4], c[4];
+    if (k + 4 <= D) {
+      const F4u a = *reinterpret_cast<const F4u *>(xr + k), b = *reinterpret_cast<const F4u *>(cr + k);
+      v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w;
+      c[0] = b.x, c[1] = b.y, c[2] = b.z, c[3] = b.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = k + e < D ? xr[k + e] : 0.f;
+        c[e] = k + e < D ? cr[k + e] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double d = has ? double(v[e]) - double(c[e]) : double(v[e]);
+      s = fma(d, d, s);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane == 0) {
+    if (!has) out_d[row] = float(s) + kFarthest;
+    else out_d[row] = s < double(__builtin_inff()) ? float(s) : __builtin_nanf("");
+  }
+}
+
+// Whether an assignment runs on split float16: where that was faster than the
+// float32 kernels at every number of rows measured (128 to 300,000).  Us,
+// float32 against split: rows that are whole 16-byte runs (matrix kernel) 65,536 x
+// 16 by 1,024 69, 92, by 4,096 201, 184; 65,536 x 128 by 512 102, 110, by 768 137,
+// 128; 65,536 x 512 by 300 248, 253, by 512 314, 262; 128 x 768 by 4,096 1,872, 139.
+// Other rows (vector ALU) 65,536 x 33 by 512 72, 84, by 2,048 230, 147; 8,192 x 99
+// by 60 41, 60, by 256 74, 45; 8,192 x 150 by 60 58, 66; 8,192 x 230 by 16 86, 84;
+// 65,536 x 1,447 by 16 1,905, 451.  Below 16 coordinates many centres are within
+// the margin of the nearest (65,536 x 1 by 20,000 770, 2,762).
+static bool assign_on_split(int64_t n, int dim, int nlist) {
+  if (dim < 16 || dim > kSplitMaxDim || n < 128) return false;
+  const int64_t table = int64_t(nlist) * dim;
+  if (dim % 4 == 0) return nlist >= 4096 || (nlist >= 512 && table >= 98304);
+  return dim >= 200 || table >= 24576;
+}
+
+// How a call is cut: pieces of `rows` rows, groups of `tiles` tiles of centres
+// (whose halves are in the workspace at a time), `shares` workgroups along a
+// group's centres.  A plan is made for a number of bytes; what does not fit in
+// them at once goes in more pieces and groups, with the same results.
+constexpr size_t kSplitBudget = size_t(64) << 20;
+struct SplitPlan {
+  int64_t rows;   // 0: no plan
+  int tiles, groups, shares, per_share, n_slab;
+  size_t tab, split, list, parts, exact, bytes;   // offsets
+};
+static SplitPlan split_layout(int64_t rows, int tiles, int dim, int nlist) {
+  SplitPlan p{};
+  const int all = (nlist + kSpN - 1) / kSpN;
+  p.rows = rows;
+  p.tiles = tiles;
+  p.groups = (all + tiles - 1) / tiles;
+  p.n_slab = (dim + kSpK - 1) / kSpK;
+  // the centres are shared out where the rows alone leave compute units idle
+  const int64_t blocks = (rows + kSpM - 1) / kSpM;
+  const int want = int(std::min<int64_t>(tiles, (512 + blocks - 1) / blocks));
+  p.per_share = (tiles + want - 1) / want;
+  p.shares = (tiles + p.per_share - 1) / p.per_share;
   size_t off = 0;
   auto take = [&](size_t b) {
-    char *r = p ? p + off : nullptr;
+    const size_t at = off;
     off += (b + 255) / 256 * 256;
-    return r;
+    return at;
   };
-  w.tiles = (nlist + kSpN - 1) / kSpN;
-  w.n_slab = (dim + kSpK - 1) / kSpK;
-  const size_t np = size_t(w.tiles) * kSpN;
-  // the centres are shared out where the rows alone leave compute units idle
-  const int64_t blocks = (n + kSpM - 1) / kSpM;
-  const int64_t want = std::min<int64_t>(w.tiles, (512 + blocks - 1) / blocks);
-  w.tiles_per_share = int((w.tiles + want - 1) / want);
-  w.shares = (w.tiles + w.tiles_per_share - 1) / w.tiles_per_share;
-  w.cnorm = reinterpret_cast<float *>(take(np * 4));
-  w.cmul = reinterpret_cast<float *>(take(np * 4));
-  w.split = reinterpret_cast<_Float16 *>(take(np * w.n_slab * 2 * kSpK * sizeof(_Float16)));
-  if (w.shares > 1) {
-    w.part_v = reinterpret_cast<float *>(take(size_t(w.shares) * n * 4));
-    w.part_i = reinterpret_cast<int32_t *>(take(size_t(w.shares) * n * 4));
+  p.exact = take(size_t(kExParts) * (sizeof(double) + sizeof(int32_t)));
+  p.tab = take(size_t(all) * kSpN * (4 * sizeof(float) + sizeof(double)));
+  p.split = take(size_t(tiles) * kSpN * p.n_slab * 2 * kSpK * sizeof(_Float16));
+  p.list = take((size_t(rows) + 64) * 4);   // the length, then the rows
+  p.parts = take(size_t(rows) * 4 + size_t(p.groups) * p.shares * rows * 12);
+  p.bytes = off;
+  return p;
+}
+static SplitPlan split_plan(int64_t n, int dim, int nlist, size_t budget) {
+  const int all = (nlist + kSpN - 1) / kSpN;
+  const int64_t least = std::min<int64_t>(n, 4096);   // a smaller piece does not pay
+  int64_t rows = std::min<int64_t>(n, int64_t(1) << 24);
+  for (int tiles = all; tiles >= 1; tiles = (tiles + 1) / 2) {
+    for (int64_t r = rows; r >= least; r = r > least ? std::max(least, (r / 2 + 255) / 256 * 256) : 0) {
+      const SplitPlan p = split_layout(r, tiles, dim, nlist);
+      if (p.bytes <= budget) return p;
+    }
+    if (tiles == 1) break;
   }
-  w.bytes = off;
-  return w;
+  return SplitPlan{};
+}
+
+static int launch_assign_split(const SplitPlan &p, const float *x, int64_t n, int dim, const float *cen,
+                               int nlist, int32_t *out_ids, float *out_d, void *ws, hipStream_t s) {
+  char *w = static_cast<char *>(ws);
+  const int all = (nlist + kSpN - 1) / kSpN;
+  const size_t np = size_t(all) * kSpN;
+  double *part_v = reinterpret_cast<double *>(w + p.exact);
+  int32_t *part_i = reinterpret_cast<int32_t *>(part_v + kExParts);
+  CentreTab tab;
+  tab.norm = reinterpret_cast<double *>(w + p.tab);
+  tab.base = reinterpret_cast<float *>(tab.norm + np);
+  tab.along = tab.base + np;
+  tab.margin = tab.along + np;
+  tab.mul = tab.margin + np;
+  _Float16 *split = reinterpret_cast<_Float16 *>(w + p.split);
+  int32_t *n_listed = reinterpret_cast<int32_t *>(w + p.list), *list = n_listed + 64;
+  float *xnorm = reinterpret_cast<float *>(w + p.parts);
+  const int shares = p.groups * p.shares;
+  for (int64_t r0 = 0; r0 < n; r0 += p.rows) {
+    const int64_t m = std::min(p.rows, n - r0);
+    const float *xp = x + r0 * dim;
+    int st;
+    SplitPart part;
+    part.w1 = xnorm + p.rows;
+    part.w2 = part.w1 + int64_t(shares) * m;
+    part.id = reinterpret_cast<int32_t *>(part.w2 + int64_t(shares) * m);
+    int done = 0;
+    for (int g = 0; g < p.groups; ++g) {
+      const int t0 = g * p.tiles, nt = std::min(p.tiles, all - t0);
+      const int sh = (nt + p.per_share - 1) / p.per_share;
+      hipLaunchKernelGGL(k_split_centres, dim3(unsigned(nt * kSpN / 4)), dim3(256), 0, s, cen, nlist, dim,
+                         p.n_slab, t0 * kSpN, tab, split, n_listed);
+      if ((st = check_launch())) return st;
+      SplitPart pg{part.w1 + done * m, part.w2 + done * m, part.id + done * m};
+      hipLaunchKernelGGL(k_assign_split, dim3(unsigned((m + kSpM - 1) / kSpM), unsigned(sh)),
+                         dim3(kSpThreads), 0, s, xp, m, dim, p.n_slab, t0 * kSpN, tab, split, nt,
+                         p.per_share, pg, xnorm);
+      if ((st = check_launch())) return st;
+      done += sh;
+    }
+    int32_t *ids = out_ids + r0;
+    hipLaunchKernelGGL(k_assign_decide, dim3(unsigned((m + 255) / 256)), dim3(256), 0, s, m, done, part,
+                       xnorm, tab, list, n_listed, ids);
+    if ((st = check_launch())) return st;
+    hipLaunchKernelGGL(k_assign_exact, dim3(kExGrid), dim3(256), 0, s, xp, dim, cen, nlist, tab.norm,
+                       list, n_listed, part_v, part_i, ids);
+    if ((st = check_launch())) return st;
+    if (out_d)
+      hipLaunchKernelGGL(k_assign_finish, dim3(unsigned((m + 3) / 4)), dim3(256), 0, s, xp, m, dim, cen,
+                         nlist, n_listed, part_v, part_i, ids, out_d + r0);
+    else
+      hipLaunchKernelGGL(k_assign_listed, dim3(256), dim3(256), 0, s, list, n_listed, nlist, part_v,
+                         part_i, ids);
+    if ((st = check_launch())) return st;
+  }
+  return RSLM_OK;
+}
+
+// The least workspace a call accepts: the float32 kernels' scratch.
+static size_t probe_min_workspace(int64_t n, int32_t nlist, int mode) {
+  const size_t norms = (size_t(nlist) * sizeof(float) + 255) / 256 * 256;
+  if (mode == IVF_ASSIGN_L2) return norms;
+  return norms + (size_t(n) * size_t(nlist) * sizeof(float) + 255) / 256 * 256;
 }
 
 // Probe dots for many rows (D a multiple of 4, 16-byte aligned operands): one
@@ -1081,19 +1405,10 @@ size_t ivf_assign_probe_workspace(int64_t n, int32_t dim, int32_t nlist, int32_t
                                   int mode) {
   (void)nprobe;
   if (n < 0 || nlist < 1) return 0;
-  const size_t norms = (size_t(nlist) * sizeof(float) + 255) / 256 * 256;
+  const size_t least = probe_min_workspace(n, nlist, mode);
   if (mode == IVF_ASSIGN_L2 && dim >= 1 && nlist <= 65536 && assign_on_split(n, dim, nlist))
-    return assign_split_ws(nullptr, n, dim, nlist).bytes;
-  if (mode == IVF_ASSIGN_L2) return norms;
-  const size_t dots = size_t(n) * size_t(nlist) * sizeof(float);
-  return norms + (dots + 255) / 256 * 256;
-}
-
-// The least a call accepts: the float32 kernels' scratch.
-static size_t probe_min_workspace(int64_t n, int32_t nlist, int mode) {
-  const size_t norms = (size_t(nlist) * sizeof(float) + 255) / 256 * 256;
-  if (mode == IVF_ASSIGN_L2) return norms;
-  return norms + (size_t(n) * size_t(nlist) * sizeof(float) + 255) / 256 * 256;
+    return std::max(least, split_plan(n, dim, nlist, kSplitBudget).bytes);
+  return least;
 }
 
 int ivf_assign_probe(const float *x, int64_t n, int32_t dim, const float *centroids,
@@ -1109,25 +1424,12 @@ int ivf_assign_probe(const float *x, int64_t n, int32_t dim, const float *centro
     return RSLM_ERR_INVALID_ARG;
   if (!ws || ws_bytes < probe_min_workspace(n, nlist, mode)) return RSLM_ERR_WORKSPACE;
   hipStream_t s = as_stream(stream);
-  if (mode == IVF_ASSIGN_L2 && (n + 255) / 256 <= 0x7fffffff && (n + 3) / 4 <= 0x7fffffff &&
-      assign_on_split(n, dim, nlist)) {
-    // (a workspace that has room for the norms only takes the float32 kernels)
-    const SplitWs w = assign_split_ws(ws, n, dim, nlist);
-    if (ws_bytes >= w.bytes && (reinterpret_cast<uintptr_t>(ws) & 15) == 0) {
-      hipLaunchKernelGGL(k_split_centres, dim3(unsigned(w.tiles * kSpN / 4)), dim3(256), 0, s,
-                         centroids, nlist, dim, w.n_slab, w.cnorm, w.cmul, w.split);
-      int st = check_launch();
-      if (st) return st;
-      float *bv = w.shares > 1 ? w.part_v : out_scores;
-      int32_t *bi = w.shares > 1 ? w.part_i : out_ids;
-      hipLaunchKernelGGL(k_assign_split, dim3(unsigned((n + kSpM - 1) / kSpM), unsigned(w.shares)),
-                         dim3(kSpThreads), 0, s, x, n, dim, w.n_slab, w.cnorm, w.cmul, w.split,
-                         w.tiles, w.tiles_per_share, bv, bi);
-      if ((st = check_launch())) return st;
-      hipLaunchKernelGGL(k_assign_finish, dim3(unsigned((n + 3) / 4)), dim3(256), 0, s, x, n, dim,
-                         centroids, nlist, w.cnorm, w.shares, bv, bi, out_ids, out_scores);
-      return check_launch();
-    }
+  if (mode == IVF_ASSIGN_L2 && assign_on_split(n, dim, nlist) &&
+      (reinterpret_cast<uintptr_t>(ws) & 15) == 0) {
+    // (a workspace too small for pieces of a useful size takes the float32 kernels)
+    const SplitPlan pl = split_plan(n, dim, nlist, std::min(ws_bytes, kSplitBudget));
+    if (pl.rows > 0)
+      return launch_assign_split(pl, x, n, dim, centroids, nlist, out_ids, out_scores, ws, s);
   }
   if (mode == IVF_ASSIGN_L2) {
     float *cnorm = static_cast<float *>(ws);
