@@ -1573,6 +1573,8 @@ bool launch_score_mfma(const rslm_plan *p, const uint8_t *records, int64_t n_poo
                        int64_t n, const float *q_rot, int Q, float *out, hipStream_t s) {
   const CodecParams &cp = p->codec;
   if (cp.lead > 0 || cp.D > 1024) return false;
+  // a lane whose id names no record reads record 0's scales: there has to be one
+  if (n_pool < 1) return false;
   // from about 4,096 records on the table fill is paid for (us, k_score_reg
   // against this: 5,000 of D = 300, 3 bits 20, 9; of D = 1,000, 1 bit 25, 15; 100,000
   // of D = 128, 4 bits 14, 9)

@@ -4,6 +4,8 @@ at the very end of the pool) against float64 scores of the same records.
 The bound is that of a float32 dot product: D / 32 + 8 roundings of partial
 sums no larger than ||q|| ||C[code]||, times the two scales."""
 
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -72,3 +74,22 @@ def test_special_queries(bits):
     sign = np.sign(chat[:, 7])
     assert np.all(got[2][sign != 0] == np.inf * sign[sign != 0])
     assert np.isnan(got[3]).all()
+
+
+@pytest.mark.parametrize("D,bits,mode", [(64, 4, "global"), (300, 3, "local"), (1024, 1, "global")])
+@pytest.mark.parametrize("Q", [1, 5])
+def test_empty_pool(D, bits, mode, Q):
+    """No record to read: every id is outside the pool and scores -inf (through the C
+    entry point, as torch gives an empty tensor a null pointer)."""
+    import paper_2608_30384_amd as R
+    from paper_2608_30384_amd import _lib as L
+    plan = R.Plan(D, bits, passes=1, scale_mode=mode)
+    n = 8192
+    pool = torch.zeros(16, dtype=torch.uint8, device=DEV)
+    ids = torch.randint(-3, 4, (n,), device=DEV)
+    q = torch.randn(Q, D, device=DEV)
+    out = torch.full((Q, n), 7.0, device=DEV)
+    p = lambda t: C.c_void_p(t.data_ptr())  # noqa: E731
+    assert L.lib().rslm_score(plan.handle, p(pool), 0, p(ids), n, p(q), Q, p(out),
+                              C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    assert bool(torch.isneginf(out).all())
