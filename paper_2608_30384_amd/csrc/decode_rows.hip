@@ -30,14 +30,16 @@ __global__ void __launch_bounds__(256, NBR <= 4 ? 4 : 2) k_decode_rows(
   uint16_t *ts = reinterpret_cast<uint16_t *>(lds + 4 * VPW * stride);
   RowsTs<128 * RPV * NBR> tload;
   tload.load(rp);
+  RowsSigns signs;
+  signs.load(rp);
   if (tid < 16) {
     if (G == 1) cbs[tid] = cp.cb[tid];
     if (G == 2) cb4[tid] = make_float4(cp.cb[2 * tid], cp.cb[2 * tid + 1], 0.f, 0.f);
     if (G == 4) cb4[tid] = make_float4(cp.cb[4 * tid], cp.cb[4 * tid + 1], cp.cb[4 * tid + 2], cp.cb[4 * tid + 3]);
     if (LITE) cb8[tid] = cp.cb_lead[tid & 7];
   }
-  tload.store(ts, rp, false);
-  rows_fill_signs(s1, rp);
+  tload.store(ts, rp, signs, false);
+  signs.fill(s1, rp);
   __syncthreads();
   const int64_t n_groups = (n + VPW - 1) / VPW;
   for (int64_t grp = int64_t(blockIdx.x) * 4 + wid; grp < n_groups; grp += int64_t(gridDim.x) * 4) {
@@ -167,13 +169,13 @@ static void launch_decode_t(const DecodeCall &c) {
   const int D = c.p->rot.D;
 #define RSLM_DECODE_ROWS(RPV, NBR)                                                     \
   {                                                                                    \
-    if (RPV * NBR == 1 || D == 128 * RPV * NBR)                                        \
+    if (rows_only_full(RPV, NBR) || D == 128 * RPV * NBR)                              \
       launch_decode_one<RPV, NBR, BITS, LITE, true>(c);                                \
     else                                                                               \
-      launch_decode_one<RPV, NBR, BITS, LITE, RPV * NBR == 1>(c);                      \
+      launch_decode_one<RPV, NBR, BITS, LITE, rows_only_full(RPV, NBR)>(c);            \
   }
   const int nbt = rows_blocks(c.p->rot);
-  RSLM_ROWS_SWITCH(nbt, RSLM_DECODE_ROWS)
+  RSLM_ROWS_SWITCH(nbt, D == 384, RSLM_DECODE_ROWS)
 #undef RSLM_DECODE_ROWS
 }
 

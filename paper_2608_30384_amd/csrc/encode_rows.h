@@ -47,9 +47,13 @@ struct __attribute__((packed, aligned(1))) U64u {
 // NB and 1-D codebooks, and a vector in LDS for the rest: 65,536 x 768 4-bit +
 // SQ8 171 -> 123; 524,288 x 768 two-stage 1,314 -> 998; 65,536 x 1,024 2-bit 816
 // -> 150; 65,536 x 2,049 4-bit 1,307 -> 288 (kernel); 153,633 x 698
-// two-stage 1,425 -> 395.  At D = 128 and 256 with 1-D codebooks (one row
-// either way): 1,000,000 x 128 194 -> 180, 700,000 x 256 295 -> 271, but calls of
-// 12 to 18 us take about 1 us longer (30,000 x 128: 12.0 -> 13.0).
+// two-stage 1,425 -> 395.  At D = 128, 256 and 384 with 1-D codebooks (one row
+// either way) 400,000 x 128 + SQ8 100 -> 94, 400,000 x 384 276 -> 210.  Calls of a
+// few thousand vectors are one wavefront's chain of waits (arguments, tables,
+// record, centre, LDS lookups): with the sign words looked up where they are
+// used, a record's list loaded after its row and one coordinate quantised after
+// the other, 2,000 x 128 took 4.8 us and 2,000 x 128 two-stage 6.5; 4.2 and 6.2
+// here (4.2 and 6.3 with one row per vector and the tables of one dimension).
 template <int RPV, int NBR, int BITS, bool LITE, bool TWO, bool FULL>
 __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 4 : NBR <= 5 ? 3 : 2) k_encode_rows(EncodeArgs a) {
   constexpr int E = 8 * NBR;
@@ -84,20 +88,20 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
   // 2-D and 4-D codebooks (their codes are those of the LDS path)
   const bool mid = (!FULL && rp.overlap) || G > 1;
 
+  // the arguments that the first loads need, in one go (the compiler would fetch
+  // each behind the branch on the one before)
+  asm volatile("" ::"s"(a.n_records), "s"(a.src_row), "s"(a.cen), "s"(a.rec_list), "s"(rp.passes), "s"(rp.tsrc));
   const int64_t n_groups = (a.n_records + VPW - 1) / VPW;
   const int64_t step = int64_t(gridDim.x) * 4;
-  // source row and list of this lane's record of group g; row < 0: none
+  // source row and list of this lane's record of group g (both loads in
+  // flight at once: looked at when the group's turn comes)
   auto fetch = [&](int64_t g, int64_t &row, int &L) {
     const int64_t rec = g * VPW + (lane >> 4) / RPV;
     row = -1;
     L = -1;
     if (rec < a.n_records) {
       row = a.src_row ? a.src_row[rec] : rec;
-      if (row >= a.n_rows) row = -1;
-      if (a.cen) {
-        L = a.rec_list[rec];
-        if (L < 0 || L >= a.nlist) row = -1;
-      }
+      if (a.cen) L = a.rec_list[rec];
     }
   };
   int64_t nrow;
@@ -108,6 +112,8 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
   // memory once before its first record.
   RowsTs<128 * RPV * NBR> tload;
   tload.load(rp);
+  RowsSigns signs;
+  signs.load(rp);
   constexpr int kG2 = kGrid2 * kGrid2 / 256;
   uint16_t gv1[G == 2 ? kG2 : 1], gv2[TWO ? kG2 : 1];
   if (G == 2) {
@@ -155,7 +161,7 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
       cnt += quant_bucket(cp.thr_lead[k], cp.qs_lead, cp.qo_lead, cp.qn_lead) < tid;
     qtab8[tid] = uint8_t(cnt);
   }
-  tload.store(ts, rp, !mid);
+  tload.store(ts, rp, signs, !mid);
   if (tid < 16) {
     if constexpr (G == 1) {
       cbs[tid] = cbv[0];
@@ -191,12 +197,13 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
       }
     }
   }
-  rows_fill_signs(s1, rp);
+  signs.fill(s1, rp);
   __syncthreads();
 
   for (int64_t grp = int64_t(blockIdx.x) * 4 + wid; grp < n_groups; grp += step) {
-    const int64_t row = nrow;
     const int L = nL;
+    const bool none = nrow < 0 || nrow >= a.n_rows || (a.cen && (L < 0 || L >= a.nlist));
+    const int64_t row = nrow;
     // the lane's place, opaque here: the compiler would otherwise keep every
     // address and bound derived from it in registers across the loop
     int olane = lane;
@@ -209,7 +216,7 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
     fetch(grp + step, nrow, nL);
     // rows without a vector sit the iteration out (rows of different vectors
     // never exchange data, and no workgroup barrier follows)
-    if (row < 0) continue;
+    if (none) continue;
 
     // residual r = x - c, its sums, and S1
     const int c0 = 128 * pv + 8 * r;   // this lane's first coordinate of block j is c0 + 128 RPV j
@@ -318,13 +325,24 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
         const uint8_t *qt = lb ? qtab8 : qtab;
         const float qs = lb ? cp.qs_lead : cp.qs, qo = lb ? cp.qo_lead : cp.qo;
         const int qn = lb ? cp.qn_lead : cp.qn;
+        // the three dependent lookups of a coordinate, eight coordinates at a
+        // time (left to itself the compiler takes one after the other to save
+        // registers: 24 waits for LDS a block, which few wavefronts hide)
+        float u[8];
+        uint32_t code[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const float u = z[8 * j + i] * inv_s0;
-          const uint32_t base = qt[quant_bucket(u, qs, qo, qn)];
-          const uint32_t code = base + ((u > tb[base]) ? 1u : 0u);
-          w |= code << (W * i);
-          v[i] = cbb[code];
+          u[i] = z[8 * j + i] * inv_s0;
+          code[i] = qt[quant_bucket(u[i], qs, qo, qn)];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) code[i] += (u[i] > tb[code[i]]) ? 1u : 0u;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          w |= code[i] << (W * i);
+          v[i] = cbb[code[i]];
         }
       } else if constexpr (G == 2) {
 #pragma unroll
@@ -350,7 +368,7 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
           v[2 * k + 1] = q.y;
         }
       } else {
-float u[8], best[2] = {3.4e38f, 3.4e38f};
+        float u[8], best[2] = {3.4e38f, 3.4e38f};
         uint32_t code[2] = {0u, 0u};
 #pragma unroll
         for (int t = 0; t < 8; ++t) u[t] = z[8 * j + t] * inv_s0;
@@ -636,13 +654,13 @@ template <int BITS, bool LITE, bool TWO>
 void launch_encode_rows(const EncodeArgs &a, hipStream_t s) {
 #define RSLM_ENCODE_ROWS(RPV, NBR)                                             \
   {                                                                            \
-    if (RPV * NBR == 1 || a.rp.D == 128 * RPV * NBR)                           \
+    if (rows_only_full(RPV, NBR) || a.rp.D == 128 * RPV * NBR)                 \
       launch_encode_one<RPV, NBR, BITS, LITE, TWO, true>(a, s);                \
     else                                                                       \
-      launch_encode_one<RPV, NBR, BITS, LITE, TWO, RPV * NBR == 1>(a, s);      \
+      launch_encode_one<RPV, NBR, BITS, LITE, TWO, rows_only_full(RPV, NBR)>(a, s); \
   }
   const int nbt = rows_blocks(a.rp);
-  RSLM_ROWS_SWITCH(nbt, RSLM_ENCODE_ROWS)
+  RSLM_ROWS_SWITCH(nbt, a.rp.D == 384, RSLM_ENCODE_ROWS)
 #undef RSLM_ENCODE_ROWS
 }
 

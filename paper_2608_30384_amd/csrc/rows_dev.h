@@ -161,10 +161,21 @@ struct RowsLane {
 // every 256 coordinates), word (16 p + r) 8 + i of an LDS table: one lane's
 // words are two 16-byte reads.
 constexpr int kSignWords = 256;
-__device__ __forceinline__ void rows_fill_signs(uint32_t *tab, const RotParams &rp) {
-  for (int c = threadIdx.x; c < kSignWords; c += blockDim.x)
-    tab[c] = rp.passes > 0 ? sign_bit(rp.s1mask, c) << 31 : 0u;
-}
+// The sign words of a thread of 256: of S1 at coordinate t, and of S2 at t (S1 at
+// t + 127); both repeat every 256.  In two steps as RowsTs: a select among the
+// mask's words would be an indexed load from the kernel's arguments at the place
+// of use, one wait for memory after another before a workgroup's first record.
+struct RowsSigns {
+  uint32_t w1, w2;
+  __device__ __forceinline__ void load(const RotParams &rp) {
+    w1 = rp.s1mask[threadIdx.x >> 5];
+    w2 = rp.s1mask[((threadIdx.x + 127) >> 5) & 7];
+  }
+  __device__ __forceinline__ void fill(uint32_t *tab, const RotParams &rp) const {
+    tab[threadIdx.x] = rp.passes > 0 ? (w1 >> (threadIdx.x & 31)) << 31 : 0u;
+  }
+  __device__ __forceinline__ uint32_t s2() const { return (w2 >> ((threadIdx.x + 127) & 31)) & 1u; }
+};
 // S1 times the lane's 8 coordinates v of block b.
 __device__ __forceinline__ void rows_flip(float (&v)[8], const uint32_t *tab, int b, int r) {
   const uint4 *p = reinterpret_cast<const uint4 *>(tab + 128 * (b & 1) + 8 * r);
@@ -189,14 +200,15 @@ struct RowsTs {
     for (int u = 0; u < (N + 255) / 256; ++u)
       src[u] = rp.tsrc[min(int(threadIdx.x) + 256 * u, rp.D - 1)];
   }
-  __device__ __forceinline__ void store(uint16_t *ts, const RotParams &rp, bool lane_sign) const {
+  __device__ __forceinline__ void store(uint16_t *ts, const RotParams &rp, const RowsSigns &sg,
+                                        bool lane_sign) const {
     if (rp.passes != 2) return;
 #pragma unroll
     for (int u = 0; u < (N + 255) / 256; ++u) {
       const int o = threadIdx.x + 256 * u;
       // the tail [128 n_full, D) is not transformed with the full blocks, but
       // with a tail lane_sign is not set
-      uint32_t s = sign_bit(rp.s1mask, o + 127);
+      uint32_t s = sg.s2();
       if (lane_sign) s ^= __popc((src[u] >> 3) & 15) & 1u;
       if (o < N) ts[o] = o < rp.D ? uint16_t(uint32_t(4 * src[u]) | (s << 15)) : uint16_t(0);
     }
@@ -411,10 +423,15 @@ __device__ __forceinline__ void rows_inverse(float (&z)[8 * NBR], const RotParam
 // coordinates (reductions and scalar steps are per row), then four.  Always
 // more than RPV (NBR - 1) blocks, so that the blocks j < NBR - 1 of every row
 // are full and only the last one can be the tail or past the end; kernels have
-// an instantiation (FULL) for D = 128 RPV NBR, where none is.
-#define RSLM_ROWS_SWITCH(NBT, CALL)  \
+// an instantiation (FULL) for D = 128 RPV NBR, where none is.  D = 384 (EXACT)
+// has an arrangement of its own: with two rows of two blocks one of the four
+// is past the end, and its last blocks are read and written element by element
+// (4-bit encode with a 2-bit second stage, us: 8,000 x 384 33.2, 15.7 here; 400,000
+// 1,062, 350).
+#define RSLM_ROWS_SWITCH(NBT, EXACT, CALL)  \
   if ((NBT) <= 1) CALL(1, 1)         \
   else if ((NBT) <= 2) CALL(1, 2)    \
+  else if ((NBT) == 3 && (EXACT)) CALL(1, 3) \
   else if ((NBT) <= 4) CALL(2, 2)    \
   else if ((NBT) <= 6) CALL(2, 3)    \
   else if ((NBT) <= 8) CALL(2, 4)    \
@@ -425,6 +442,8 @@ __device__ __forceinline__ void rows_inverse(float (&z)[8 * NBR], const RotParam
   else if ((NBT) <= 28) CALL(4, 7)   \
   else CALL(4, 8)
 
+// Arrangements that are only used where D = 128 RPV NBR.
+constexpr bool rows_only_full(int rpv, int nbr) { return rpv == 1 && nbr != 2; }
 inline bool rows_ok(const RotParams &rp) { return rp.B == 128 && rp.D >= 128 && rp.D <= kMaxDim; }
 inline int rows_blocks(const RotParams &rp) { return rp.n_full + (rp.overlap ? 1 : 0); }
 

@@ -26,8 +26,8 @@ R = parity.R
 # s^ is within 1e-5 of a rounding midpoint, and where it rounds the other way,
 # s^ moves by 2^-10 and its g^ by more than the one 2^-12 code allowed for all
 # rows by the shared check.)
-DIMS = [(128, 3, 2), (129, 4, 1), (255, 1, 2), (256, 2, 2), (257, 2, 2), (300, 1, 2), (386, 4, 2),
-        (512, 3, 2), (513, 2, 2), (640, 1, 2), (700, 3, 2), (769, 4, 2), (1000, 2, 2), (1024, 1, 1),
+DIMS = [(128, 3, 2), (129, 4, 1), (255, 1, 2), (256, 2, 2), (257, 2, 2), (300, 1, 2), (384, 4, 2),
+        (384, 2, 1), (386, 4, 2), (512, 3, 2), (513, 2, 2), (640, 1, 2), (700, 3, 2), (769, 4, 2), (1000, 2, 2), (1024, 1, 1),
         (1025, 4, 2), (1500, 3, 2), (1537, 1, 2), (2047, 2, 2), (2049, 2, 2), (2560, 4, 2),
         (2561, 1, 2), (3000, 4, 2), (3073, 3, 2), (3584, 2, 2), (3585, 4, 0), (4096, 4, 2)]
 
@@ -44,6 +44,7 @@ def test_decode(R, D, bits, passes):
 
 @pytest.mark.parametrize("D,bits,passes,mode2,n", [
     (129, 4, 1, "global", 37), (255, 2, 2, "local", 41), (300, 1, 2, "global", 50),
+    (384, 4, 2, "global", 35), (384, 1, 2, "local", 18),
     (385, 3, 2, "global", 33), (640, 4, 2, "local", 30), (1025, 2, 2, "global", 27),
     (1537, 4, 2, "global", 21), (2561, 3, 2, "global", 18), (3585, 4, 2, "global", 19),
     (4096, 1, 2, "local", 18)])
@@ -52,6 +53,7 @@ def test_encode_two_stage(R, D, bits, passes, mode2, n):
 
 
 @pytest.mark.parametrize("D,passes,n,lite", [(129, 1, 61, False), (255, 2, 77, True), (300, 2, 90, False),
+                                             (384, 2, 49, False), (384, 2, 83, True),
                                              (700, 2, 66, True), (1025, 2, 70, False),
                                              (2049, 2, 75, True), (3001, 2, 60, False),
                                              (4096, 2, 51, False)])
