@@ -445,6 +445,7 @@ struct ScanArgs {
   int n_pass;             // passes over ranges of NC chunks (NC * n_pass = n_chunks)
   int lead;               // Rslm4Lite: leading coordinates on the K = 8 codebook (16 or 32)
   int global;             // Rslm4Lite: the global scale is embedded too
+  int home_items;         // up to this many items each has a workgroup of its queue's XCD
   float cb_lead[8];       // Rslm4Lite: the K = 8 codebook
 };
 
@@ -758,10 +759,20 @@ __global__ void __launch_bounds__(kScanThreads, 2) k_scan(ScanArgs a) {
       for (int w = 0; w < T::kWords; ++w) dtab[idx * T::kWords + w] = a.dtab[e * T::kWords + w];
     }
   }
-  // a workgroup beyond the number of items would only search eight empty
-  // queues (and contend for their counters with those that have work)
+  // A workgroup for which its XCD's queue has no item would only search the
+  // queues for what others take (and contend for their counters): it leaves,
+  // where every item has a workgroup on its own queue's XCD (workgroups go to
+  // the XCDs in turn).  Every workgroup past the number of items leaving sends
+  // items to other XCDs' workgroups, one failed ticket after another; none
+  // leaving costs the contention.  Whole search, us, past the number of items,
+  // none, these: 138 queries of about 370 items at 2 bits, D = 1,536 111, 107, 109;
+  // 2 of about 60 at 3 bits, D = 1,168 91, 86, 85; 8 of about 600 at 2 bits, D = 128
+  // 78, 88, 78; 13 of about 90 at 4 bits, D = 256 46, 50, 46.
   const int n_items = __builtin_amdgcn_readfirstlane(n_items_v);
-  if (int(blockIdx.x) >= n_items) return;
+  if (n_items <= a.home_items) {
+    const int rank = int(blockIdx.x) / kQueues, home = int(blockIdx.x) & (kQueues - 1);
+    if (((rank & -kQueueBlock) * kQueues | home * kQueueBlock | (rank & (kQueueBlock - 1))) >= n_items) return;
+  }
   __syncthreads();
 
   const int m = lane & 15;           // A row / B column of this lane
@@ -1708,8 +1719,12 @@ int rslm_scan_topk(const rslm_plan *p, const rslm_index *idx, const float *q_rot
   // byte tables of 2 and 1 bits from 24 chunks up)
   const bool big_table = p->codec.bits == 4 || (p->codec.bits <= 2 && nc_pass >= 24);
   const int wg_per_cu = big_table ? 2 : 4;
-  const dim3 grid(unsigned(std::min<int64_t>(
-      cu_count() * wg_per_cu, scan_max_items(Q, nprobe, nlist, idx->max_list_size, chunk))));
+  // (a workgroup per item on its queue's XCD: whole rounds of the queues' blocks)
+  constexpr int kRound = kQueues * kQueueBlock;
+  const int64_t rounds = (scan_max_items(Q, nprobe, nlist, idx->max_list_size, chunk) + kRound - 1) / kRound;
+  const dim3 grid(unsigned(std::min<int64_t>(cu_count() * wg_per_cu, rounds * kRound)));
+  const int ranks = int(grid.x) / kQueues;
+  a.home_items = ranks / kQueueBlock * kRound + ranks % kQueueBlock;   // queue_item(0, ranks)
   switch (p->codec.bits) {
     case 4:
       if (a.lead > 0) launch_scan_bits<4, true>(nc_pass, n_pass > 1, grid, s, a);
