@@ -363,6 +363,9 @@ typedef struct rslm_index {
  *   coordinates are scored in passes over equal chunk ranges).  With a Lite
  *   plan the scales are read from the codes (the index's scales array is not
  *   used and may be NULL).
+ *   Workspace: small calls ask for more, for descriptors of small work items;
+ *   one with room for those of full-size items (2,048 candidates) is accepted
+ *   too, with the same results, and a smaller one returns RSLM_ERR_WORKSPACE.
  * ------------------------------------------------------------------------ */
 size_t rslm_scan_topk_workspace(const rslm_plan *plan, const rslm_index *index,
                                 int32_t Q, int32_t nprobe, int32_t k);

@@ -86,10 +86,13 @@ struct ScanWs {
 // Work items of a call, at most: (groups of <= 8 queries) x (chunks of the
 // longest list); groups <= npairs / 8 + (number of probed lists), and no more
 // than one per pair.
-static int64_t scan_max_items(int Q, int nprobe, int nlist, int max_list, int chunk) {
+static int64_t scan_max_groups(int Q, int nprobe, int nlist) {
   const int64_t npairs = int64_t(Q) * nprobe;
-  const int64_t groups = npairs / kGroupQ + std::min<int64_t>(nlist, npairs);
-  return groups * std::max<int64_t>(1, (int64_t(max_list) + chunk - 1) / chunk);
+  return std::min<int64_t>(npairs, npairs / kGroupQ + nlist);
+}
+static int64_t scan_max_items(int Q, int nprobe, int nlist, int max_list, int chunk) {
+  return scan_max_groups(Q, nprobe, nlist) *
+         std::max<int64_t>(1, (int64_t(max_list) + chunk - 1) / chunk);
 }
 
 // Most candidates of a work item.  2,048 where the call has items enough for
@@ -102,9 +105,7 @@ static int64_t scan_max_items(int Q, int nprobe, int nlist, int max_list, int ch
 // kernel 26.8 us with 2,048-candidate items on
 // the full grid, 6.3 us with these.
 static int scan_chunk(int Q, int nprobe, int nlist, int max_list) {
-  const int64_t npairs = int64_t(Q) * nprobe;
-  const int64_t groups = std::min<int64_t>(npairs, npairs / kGroupQ + nlist);
-  const int64_t per = groups * (int64_t(max_list) / 2) / 512;
+  const int64_t per = scan_max_groups(Q, nprobe, nlist) * (int64_t(max_list) / 2) / 512;
   int chunk = kChunkMin;
   while (chunk < kChunkCands && chunk < per) chunk *= 2;
   return chunk;
