@@ -67,8 +67,8 @@ __global__ void __launch_bounds__(256, NBR <= 4 ? 4 : 2) k_decode_rows(
       const int q = min(16 * (j * RPV + pv) + r, q_end - 1);
       const int off = (q >> 2) * BITS;
       const uint8_t *p = tile + 256 * (q & 3);
-      if (BITS == 4) word[j] = *reinterpret_cast<const uint32_t *>(p + (off >> 4) * 1024 + (off & 15));
-      else if (BITS == 2) word[j] = *reinterpret_cast<const uint16_t *>(p + (off >> 4) * 1024 + (off & 15));
+      if (BITS == 4) word[j] = reinterpret_cast<const U32u *>(p + (off >> 4) * 1024 + (off & 15))->v;
+      else if (BITS == 2) word[j] = reinterpret_cast<const U16u *>(p + (off >> 4) * 1024 + (off & 15))->v;
       else if (BITS == 1) word[j] = p[(off >> 4) * 1024 + (off & 15)];
       else
         word[j] = uint32_t(p[(off >> 4) * 1024 + (off & 15)]) |

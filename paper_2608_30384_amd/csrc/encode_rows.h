@@ -31,13 +31,6 @@ struct EncodeArgs {
 // codebooks have 128; larger grids take the general path).
 constexpr int kQuantBuckets = 128;
 
-struct __attribute__((packed, aligned(1))) U16u {
-  uint16_t v;
-};
-struct __attribute__((packed, aligned(1))) U64u {
-  uint32_t a, b;
-};
-
 // Bound by VALU issue: about 60 instructions per coordinate (two rotation
 // passes 16, quantiser 12 for 1-D codebooks, the rest residual, norms, signs
 // and the second residual), 40 % more for 2-D and twice as many for 4-D ones.
@@ -469,9 +462,9 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
       const int off = (q >> 2) * BITS;
       uint8_t *p = tile + 256 * (q & 3);
       if (BITS == 4) {
-        *reinterpret_cast<uint32_t *>(p + (off >> 4) * 1024 + (off & 15)) = w;
+        reinterpret_cast<U32u *>(p + (off >> 4) * 1024 + (off & 15))->v = w;
       } else if (BITS == 2) {
-        *reinterpret_cast<uint16_t *>(p + (off >> 4) * 1024 + (off & 15)) = uint16_t(w);
+        reinterpret_cast<U16u *>(p + (off >> 4) * 1024 + (off & 15))->v = uint16_t(w);
       } else if (BITS == 1) {
         p[(off >> 4) * 1024 + (off & 15)] = uint8_t(w);
       } else {

@@ -1,7 +1,7 @@
 // Rotation of vectors spread over 16-lane rows of a wavefront, for any D >=
 // 128 (blocks of 128, the last one overlapping its predecessor when 128 does
-// not divide D): the device code shared by the encoder, the decoder and the
-// stand-alone rotation.
+// not divide D): the device code shared by the encoder and the decoder (the
+// stand-alone rotation takes its helpers only).
 //
 // A vector takes RPV rows (1, 2 or 4) of 16 lanes, 4 / RPV vectors per
 // wavefront.  Row pv of a vector holds the 128-blocks b = j RPV + pv (j <
@@ -37,6 +37,16 @@ __device__ __forceinline__ float &lds_at(float *buf, uint32_t byte_off) {
 // Four floats at any 4-byte alignment (rows of an odd dimension).
 struct __attribute__((packed, aligned(4))) Float4u {
   float x, y, z, w;
+};
+// Words of byte arrays (packed codes) at any alignment.
+struct __attribute__((packed, aligned(1))) U16u {
+  uint16_t v;
+};
+struct __attribute__((packed, aligned(1))) U32u {
+  uint32_t v;
+};
+struct __attribute__((packed, aligned(1))) U64u {
+  uint32_t a, b;
 };
 
 constexpr int kDppQuadXor1 = 0xB1;   // quad_perm [1, 0, 3, 2]

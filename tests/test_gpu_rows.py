@@ -61,11 +61,12 @@ def test_encode_sq8(R, D, passes, n, lite):
     rescore.test_encode_sq8_parity(R, D, passes, n, lite)
 
 
-@pytest.mark.parametrize("D", [131, 300, 768, 2049])
+@pytest.mark.parametrize("D", [131, 300, 384, 768, 2049])
 def test_rows_at_any_alignment(R, D):
     """Rows of x, the centres and the outputs that start 4 bytes past a 16-byte
-    boundary (1 byte for codes2), records in any order with unused ones among
-    them: the same bytes as aligned arrays in row order."""
+    boundary (1 byte for codes and codes2), records in any order with unused ones
+    among them: the same bytes as aligned arrays in row order; and the same
+    vectors decoded from codes at any byte."""
     n, nlist, plan = 53, 4, None
     rng = np.random.default_rng(D)
     x = synth.aniso(n, D, seed=D)
@@ -77,9 +78,9 @@ def test_rows_at_any_alignment(R, D):
         t = torch.zeros(a.size + k, dtype=torch.from_numpy(a).dtype, device=DEV)[k:].view(a.shape)
         return t.copy_(torch.from_numpy(np.ascontiguousarray(a)))
 
-    def encode(xt, ct, crot, src, lists, lo, hi, codes2):
+    def encode(xt, ct, crot, src, lists, lo, hi, codes2, shift=0):
         m = lists.numel()
-        codes = torch.zeros(plan.code_bytes(m), dtype=torch.uint8, device=DEV)
+        codes = torch.zeros(plan.code_bytes(m) + shift, dtype=torch.uint8, device=DEV)[shift:]
         scales = torch.zeros(m, dtype=torch.int32, device=DEV)
         R.rslm_encode_sq8(plan, xt, codes, scales, lo, hi, codes2, n_records=m, src_row=src,
                           rec_list=lists, centroids=ct, centroids_rot=crot)
@@ -97,8 +98,23 @@ def test_rows_at_any_alignment(R, D):
     lists = np.zeros(n + 18, np.int32)
     lists[place] = assign
     b2 = off(np.zeros((n, D), np.uint8))
-    b, sb = encode(off(x), off(c32), off(crot), t(src), t(lists), off(-hi), off(hi), b2)
+    b, sb = encode(off(x), off(c32), off(crot), t(src), t(lists), off(-hi), off(hi), b2, shift=1)
     assert np.array_equal(a, b[place]) and np.array_equal(sa, sb[place])
     assert np.array_equal(a2.cpu().numpy(), b2.cpu().numpy())
     unused = np.setdiff1d(np.arange(n + 18), place)
     assert not b[unused].any() and not sb[unused].any()
+
+
+@pytest.mark.parametrize("D,bits", [(131, 4), (384, 4), (300, 3), (768, 2), (1100, 2), (513, 1)])
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_codes_at_any_byte(R, D, bits, shift):
+    plan = R.Plan(D, bits, passes=2)
+    n = 45
+    x = torch.from_numpy(synth.aniso(n, D, seed=D)).to(DEV)
+    got = []
+    for k in (0, shift):
+        codes = torch.zeros(plan.code_bytes(n) + k, dtype=torch.uint8, device=DEV)[k:]
+        scales = torch.zeros(n, dtype=torch.int32, device=DEV)
+        R.rslm_encode(plan, x, codes, scales)
+        got.append((codes, scales, R.rslm_decode(plan, codes, scales, n)))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
