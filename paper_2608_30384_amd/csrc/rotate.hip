@@ -827,7 +827,7 @@ int rslm_fwht(const rslm_plan *p, const float *x, float *y, int64_t n, int inver
 // Whether the encoder on 16-lane rows takes a call: D >= 128, quantiser tables
 // that fit it (1-D grids of at most kQuantBuckets buckets, cell lists for 2-D
 // codebooks), and a 2-bit second stage if any.  No alignment beyond the
-// element types' is assumed.
+// element types' is assumed (of the byte arrays none).
 static bool encode_on_rows(const rslm_plan *p, const rslm_plan *p2) {
   const CodecParams &cp = p->codec;
   if (!rows_ok(p->rot)) return false;
@@ -978,8 +978,7 @@ int rslm_decode(const rslm_plan *p, const uint8_t *codes, const uint32_t *scales
     return check_launch();
   const int D = p->rot.D;
   const int dstride = lds_floats(D);
-  int waves = 4;
-  while (waves > 1 && size_t(waves) * 2 * dstride * 4 > 65536) waves >>= 1;
+  constexpr int waves = 4;   // D < 128: a few KB of LDS
   const size_t shm = size_t(waves) * 2 * dstride * sizeof(float);
   const int64_t grid = (n + waves - 1) / waves;
   if (grid > 0x7fffffff) return RSLM_ERR_INVALID_ARG;
