@@ -324,6 +324,10 @@ size_t ivf_assign_probe_noalloc_limit(void);
  *   x: n x dim float32; assign: n int32; centroids: nlist x dim float32,
  *   read and written in place.  n < 2^31, nlist <= 65536, dim <= 2^20; all
  *   arrays 4-byte aligned, else RSLM_ERR_INVALID_ARG.
+ *   Workspace: calls of few centres (128 nlist <= n, nlist < 2048) ask for 8
+ *   MiB of partial float64 sums, to share a centre's points out; one without
+ *   them, or not 8-byte aligned, is accepted too and takes one workgroup per
+ *   centre and 256 coordinates.
  * ------------------------------------------------------------------------ */
 size_t ivf_kmeans_update_workspace(int64_t n, int32_t nlist);
 int ivf_kmeans_update(const float *x, int64_t n, int32_t dim, const int32_t *assign,

@@ -267,8 +267,10 @@ int ivf_kmeans_update(const float *x, int64_t n, int32_t dim, const int32_t *ass
     return RSLM_ERR_INVALID_ARG;
   const KmWs w = km_ws_layout(ws, n, nlist);
   if (!ws || ws_bytes < w.min_bytes) return RSLM_ERR_WORKSPACE;
-  // (without room for partial sums a centre's points are not shared out)
-  const int shares = (w.partial && ws_bytes >= w.bytes) ? km_shares(n, dim, nlist) : 1;
+  // (without room for partial sums, or where they would not be aligned, a
+  // centre's points are not shared out)
+  const bool part = w.partial && ws_bytes >= w.bytes && (reinterpret_cast<uintptr_t>(ws) & 7) == 0;
+  const int shares = part ? km_shares(n, dim, nlist) : 1;
   hipStream_t s = as_stream(stream);
   int st;
   hipLaunchKernelGGL(k_km_zero, dim3(unsigned((nlist + kKmThreads - 1) / kKmThreads)),
