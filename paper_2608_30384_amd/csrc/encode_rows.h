@@ -27,10 +27,6 @@ struct EncodeArgs {
   CodecParams cp, cp2;
 };
 
-// Quantiser grid buckets held in LDS (the plan's grids for the Lloyd-Max
-// codebooks have 128; larger grids take the general path).
-constexpr int kQuantBuckets = 128;
-
 // Bound by VALU issue: about 60 instructions per coordinate (two rotation
 // passes 16, quantiser 12 for 1-D codebooks, the rest residual, norms, signs
 // and the second residual), 40 % more for 2-D and twice as many for 4-D ones.
@@ -44,9 +40,10 @@ constexpr int kQuantBuckets = 128;
 // either way) 400,000 x 128 + SQ8 100 -> 94, 400,000 x 384 276 -> 210.  Calls of a
 // few thousand vectors are one wavefront's chain of waits (arguments, tables,
 // record, centre, LDS lookups): with the sign words looked up where they are
-// used, a record's list loaded after its row and one coordinate quantised after
-// the other, 2,000 x 128 took 4.8 us and 2,000 x 128 two-stage 6.5; 4.2 and 6.2
-// here (4.2 and 6.3 with one row per vector and the tables of one dimension).
+// used, the quantiser's table counted per workgroup, a record's list loaded
+// after its row and one coordinate quantised after the other, 2,000 x 128 took
+// 4.8 us and 2,000 x 128 two-stage 6.5; 3.9 and 5.9 here (4.2 and 6.3 with one row
+// per vector and the tables of one dimension).
 template <int RPV, int NBR, int BITS, bool LITE, bool TWO, bool FULL>
 __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 4 : NBR <= 5 ? 3 : 2) k_encode_rows(EncodeArgs a) {
   constexpr int E = 8 * NBR;
@@ -83,7 +80,8 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
 
   // the arguments that the first loads need, in one go (the compiler would fetch
   // each behind the branch on the one before)
-  asm volatile("" ::"s"(a.n_records), "s"(a.src_row), "s"(a.cen), "s"(a.rec_list), "s"(rp.passes), "s"(rp.tsrc));
+  asm volatile("" ::"s"(a.n_records), "s"(a.src_row), "s"(a.cen), "s"(a.rec_list), "s"(rp.passes), "s"(rp.tsrc),
+               "s"(cp.qtab));
   const int64_t n_groups = (a.n_records + VPW - 1) / VPW;
   const int64_t step = int64_t(gridDim.x) * 4;
   // source row and list of this lane's record of group g (both loads in
@@ -126,6 +124,9 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
       hiv[u] = a.sq8_hi[min(tid + 256 * u, D - 1)];
     }
   }
+  // quantiser tables of the plan
+  const uint8_t qv = G == 1 ? cp.qtab[tid & (kQuantBuckets - 1)] : 0;
+  const uint8_t qv8 = LITE ? cp.qtab[kQuantBuckets + (tid & (kQuantBuckets - 1))] : 0;
   // the codebooks (kernel arguments), entry t of 16 by thread t
   const int t16 = tid & 15;
   float cbv[G], thv = 0.f, c8v = 0.f, t8v = 0.f, c2v[3] = {};
@@ -141,20 +142,11 @@ __global__ void __launch_bounds__(256, NBR <= 1 ? 8 : NBR <= 2 ? 6 : NBR <= 3 ? 
     c2v[1] = a.cp2.cb[2 * t16 + 1];
     c2v[2] = a.cp2.cbh[t16];
   }
-  if (G == 1 && tid < kQuantBuckets) {
-    int cnt = 0;
-#pragma unroll
-    for (int k = 0; k + 1 < K; ++k) cnt += quant_bucket(cp.thr[k], cp.qs, cp.qo, cp.qn) < tid;
-    qtab[tid] = uint8_t(cnt);
-  }
-  if (LITE && tid < kQuantBuckets) {
-    int cnt = 0;
-#pragma unroll
-    for (int k = 0; k < 7; ++k)
-      cnt += quant_bucket(cp.thr_lead[k], cp.qs_lead, cp.qo_lead, cp.qn_lead) < tid;
-    qtab8[tid] = uint8_t(cnt);
-  }
   tload.store(ts, rp, signs, !mid);
+  if (tid < kQuantBuckets) {
+    if (G == 1) qtab[tid] = qv;
+    if (LITE) qtab8[tid] = qv8;
+  }
   if (tid < 16) {
     if constexpr (G == 1) {
       cbs[tid] = cbv[0];
@@ -640,7 +632,11 @@ void launch_encode_one(const EncodeArgs &a, hipStream_t s) {
                      (!TWO && a.sq8_lo ? size_t(a.rp.D + 3) / 4 * 32 : 0);
   constexpr auto kernel = k_encode_rows<RPV, NBR, BITS, LITE, TWO, FULL>;
   const int64_t groups = (a.n_records + 16 / RPV - 1) / (16 / RPV);
-  hipLaunchKernelGGL(kernel, dim3(rows_grid<kernel>(shm, groups)), dim3(256), shm, s, a);
+  // one or two blocks: short units, cheap tables (us, one unit each against
+  // striding: 150,000 x 128 33.0, 35.3; 300,000 x 128 58.9, 62.1, two-stage 102.7, 108.7;
+  // 100,000 x 256 32.1, 35.4; 1,000,000 x 128, 30 units each, 204, 178)
+  const unsigned grid = rows_grid<kernel>(shm, groups, RPV * NBR <= 2 ? 12 : 3);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), shm, s, a);
 }
 
 template <int BITS, bool LITE, bool TWO>

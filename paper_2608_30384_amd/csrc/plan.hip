@@ -34,6 +34,13 @@ static void quant_grid(const float *thr, int n, float &qs, float &qo, int &qn) {
     }
   }
 }
+// Thresholds in buckets below b.
+static uint8_t quant_below(const float *thr, int n, float qs, float qo, int qn, int b) {
+  int cnt = 0;
+  for (int k = 0; k < n && qn > 0; ++k) cnt += quant_bucket(thr[k], qs, qo, qn) < b;
+  return uint8_t(cnt);
+}
+
 
 // |C_k|^2 / 2 of a g-dimensional centroid, in float as the encoders use it.
 static float half_norm2(const float *c, int g) {
@@ -328,7 +335,9 @@ int rslm_plan_create(const rslm_plan_desc *d, rslm_plan **out) {
 
   // source index of every output of the strided transpose, x'[k M + b] = x[b B + P(k)]
   // for the first M B outputs, identity on the tail
-  int16_t *tsrc = new (std::nothrow) int16_t[D];
+  // (with the quantiser grids' tables behind it, in one allocation)
+  const size_t tsrc_bytes = sizeof(int16_t) * size_t(D) + 2 * kQuantBuckets;
+  int16_t *tsrc = new (std::nothrow) int16_t[D + kQuantBuckets];
   if (!tsrc) {
     rslm_plan_destroy(p);
     return RSLM_ERR_HIP;
@@ -337,14 +346,20 @@ int rslm_plan_create(const rslm_plan_desc *d, rslm_plan **out) {
     const int M = r.n_full, MB = r.n_full * r.B;
     for (int o = 0; o < D; ++o) tsrc[o] = int16_t(o < MB ? (o % M) * r.B + pi[o / M] : o);
   }
+  uint8_t *qtab = reinterpret_cast<uint8_t *>(tsrc + D);
+  for (int b = 0; b < kQuantBuckets; ++b) {
+    qtab[b] = quant_below(c.thr, g == 1 ? K - 1 : 0, c.qs, c.qo, c.qn, b);
+    qtab[kQuantBuckets + b] = quant_below(c.thr_lead, d->lite ? 7 : 0, c.qs_lead, c.qo_lead, c.qn_lead, b);
+  }
   hipError_t e;
-  if ((e = hipMalloc(&p->d_tsrc, sizeof(int16_t) * D)) != hipSuccess ||
-      (e = hipMemcpy(p->d_tsrc, tsrc, sizeof(int16_t) * D, hipMemcpyHostToDevice)) != hipSuccess) {
+  if ((e = hipMalloc(&p->d_tsrc, tsrc_bytes)) != hipSuccess ||
+      (e = hipMemcpy(p->d_tsrc, tsrc, tsrc_bytes, hipMemcpyHostToDevice)) != hipSuccess) {
     delete[] tsrc;
     rslm_plan_destroy(p);
     return set_hip_error(e);
   }
   delete[] tsrc;
+  c.qtab = reinterpret_cast<const uint8_t *>(p->d_tsrc + D);
   if ((e = hipMalloc(&p->d_s1, sizeof(s1f))) != hipSuccess ||
       (e = hipMalloc(&p->d_pi, sizeof(pi))) != hipSuccess ||
       (e = hipMalloc(&p->d_dtab, sizeof(uint32_t) * entries * words)) != hipSuccess) {

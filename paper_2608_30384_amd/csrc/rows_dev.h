@@ -464,14 +464,14 @@ inline int rows_blocks(const RotParams &rp) { return rp.n_full + (rp.overlap ? 1
 // later even out the ends.  Measured (us; 1, 2, 4, 8 times the resident
 // workgroups): two-stage encode of 524,288 x 768 1,177, 1,140, 1,095, 1,071 (85
 // units each at 1 x); 2-bit encode of 65,536 x 1,024 168, 164, 162, 161 (15);
-// 4-bit with SQ8 of 65,536 x 768 130, 132, 134, 140 (11).  Up to three units per
-// resident workgroup, one each: records without a vector (list padding) make
+// 4-bit with SQ8 of 65,536 x 768 130, 132, 134, 140 (11).  Up to `one_each` units
+// per resident workgroup, one each: records without a vector (list padding) make
 // units uneven, which only starting them one by one evens out (two-stage encode
 // of 20,000 x 512 34.7 against 36.4, 4-bit of 38,244 x 256 19.4 against 20.3).
 // The resident count of a kernel is kept for the last shm asked for (a query
 // takes longer than a small launch).
 template <auto kKernel>
-inline unsigned rows_grid(size_t shm, int64_t groups) {
+inline unsigned rows_grid(size_t shm, int64_t groups, int one_each = 3) {
   static std::atomic<uint64_t> kept{0};   // shm << 16 | workgroups per CU
   int cus = 0, dev = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -486,7 +486,7 @@ inline unsigned rows_grid(size_t shm, int64_t groups) {
     kept.store(uint64_t(shm) << 16 | uint64_t(per_cu), std::memory_order_relaxed);
   }
   const int64_t n = int64_t(per_cu) * cus;
-  if (groups <= 3 * n) return unsigned(std::max<int64_t>(1, groups));
+  if (groups <= one_each * n) return unsigned(std::max<int64_t>(1, groups));
   const int64_t over = std::min<int64_t>(8, std::max<int64_t>(1, (groups / n + 4) / 8));
   return unsigned(std::max<int64_t>(1, std::min(groups, n * over)));
 }

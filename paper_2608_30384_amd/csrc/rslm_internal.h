@@ -79,6 +79,9 @@ struct CodecParams {
   // each bucket holds at most one threshold; qn = 0: no such grid
   float qs, qo, qs_lead, qo_lead;
   int qn, qn_lead;
+  // the number of thresholds below each bucket, of cb (kQuantBuckets bytes),
+  // then of cb_lead, for grids of at most kQuantBuckets; device memory of the plan
+  const uint8_t *qtab;
   // 2-D codebooks: a kGrid2 x kGrid2 grid of cells over [-emax, emax]^2
   // (cell of u: floor(clamp(u_d g2s + g2o, 0, kGrid2 - 1)) per coordinate),
   // each cell listing, in ascending order, at most four codes that can be
@@ -89,6 +92,7 @@ struct CodecParams {
 };
 
 constexpr int kGrid2 = RSLM_GRID2;
+constexpr int kQuantBuckets = 128;   // the Lloyd-Max codebooks' grids have this many
 
 // Bucket of u on a uniform grid of qn buckets: floor(clamp(u qs + qo, 0,
 // qn - 1)), one fused multiply-add.  Non-decreasing in u, so with at most one
