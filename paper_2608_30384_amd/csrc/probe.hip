@@ -991,19 +991,23 @@ __global__ void __launch_bounds__(256) k_assign_finish(const float *__restrict__
 }
 
 // Whether an assignment runs on split float16: where that was faster than the
-// float32 kernels at every number of rows measured (128 to 300,000).  Us,
-// float32 against split: rows that are whole 16-byte runs (matrix kernel) 65,536 x
-// 16 by 1,024 69, 92, by 4,096 201, 184; 65,536 x 128 by 512 102, 110, by 768 137,
-// 128; 65,536 x 512 by 300 248, 253, by 512 314, 262; 128 x 768 by 4,096 1,872, 139.
-// Other rows (vector ALU) 65,536 x 33 by 512 72, 84, by 2,048 230, 147; 8,192 x 99
-// by 60 41, 60, by 256 74, 45; 8,192 x 150 by 60 58, 66; 8,192 x 230 by 16 86, 84;
-// 65,536 x 1,447 by 16 1,905, 451.  Below 16 coordinates many centres are within
-// the margin of the nearest (65,536 x 1 by 20,000 770, 2,762).
+// float32 kernels at the numbers of rows measured (128 to 1,000,000).  Us,
+// float32 against split: rows that are whole 16-byte runs (matrix kernel, tiles of
+// 128 centres) 65,536 x 16 by 1,024 69, 92, by 4,096 201, 184; 65,536 x 128 by 512
+// 102, 110, by 768 137, 128; 65,536 x 512 by 300 248, 253, by 512 314, 262; 128 x 768
+// by 4,096 1,872, 139; many rows 131,072 x 64 by 200 87, 102, x 128 by 128 92, 123, by
+// 200 130, 124; 500,000 x 768 by 128 1,258, 1,481, by 129 2,024, 1,482.  Other rows
+// (vector ALU, tiles of 64) 65,536 x 33 by 512 72, 84, by 2,048 230, 147; 8,192 x 99 by
+// 60 41, 60, by 256 74, 45; 8,192 x 150 by 60 58, 66; 8,192 x 230 by 16 86, 84; many
+// rows 65,536 x 49 by 256 61, 61; x 99 by 60 76, 77, by 128 95, 77; x 150 by 16 136, 87.
+// Below 16 coordinates many centres are within the margin of the nearest (65,536
+// x 1 by 20,000 770, 2,762).
 static bool assign_on_split(int64_t n, int dim, int nlist) {
   if (dim < 16 || dim > kSplitMaxDim || n < 128) return false;
   const int64_t table = int64_t(nlist) * dim;
-  if (dim % 4 == 0) return nlist >= 4096 || (nlist >= 512 && table >= 98304);
-  return dim >= 200 || table >= 24576;
+  if (dim % 4 == 0)
+    return nlist >= 4096 || (nlist >= 512 && table >= 98304) || (n >= 131072 && nlist > 128 && dim >= 128);
+  return dim >= 200 || table >= 24576 || (n >= 65536 && (dim >= 128 || table >= 12600));
 }
 
 // How a call is cut: pieces of `rows` rows, groups of `tiles` tiles of centres

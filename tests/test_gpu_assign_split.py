@@ -41,7 +41,8 @@ def _check(x, c, ids, dist):
     (1500, 1447, 513), (70000, 65, 16), (3000, 1, 400),
     # (on the float32 kernels: those above with few centres or coordinates)
     (128, 16, 4096), (255, 200, 512), (256, 96, 1025), (257, 36, 4097), (1000, 192, 513), (700, 230, 1),
-    (129, 67, 400), (2000, 33, 1100), (300, 1021, 257), (4573, 230, 21), (127, 230, 300)])
+    (129, 67, 400), (2000, 33, 1100), (300, 1021, 257), (4573, 230, 21), (127, 230, 300),
+    (131072, 128, 129), (65537, 131, 16), (65536, 97, 131)])
 def test_against_float64(R, n, dim, nlist):
     g = torch.Generator(device=DEV).manual_seed(n + dim)
     c = torch.randn(nlist, dim, generator=g, device=DEV) * 0.7 + 0.3
