@@ -167,7 +167,7 @@ def counter_summary(a_csv, b_csv, n_steps=5):
             ("k_plan_a", "planning, queries (a3-a5)"), ("k_plan_b", "planning, items (a3-a5)"),
             ("k_dots_tiled", "probe dots (a2)"), ("k_probe_select_reg", "probe selection (a2)"),
             ("k_rotate_reg", "query rotation (a1)"), ("k_rescore_sq8", "rescore (a6)"),
-            ("k_encode_rows<6, 4, 2,", "encode with SQ8 codes (a7)")]
+            ("k_encode_rows<2, 3, 4, false, false,", "encode with SQ8 codes (a7)")]
 
     def avg(d, part):
         ds = [v for (i, n), v in d.items() if part in n][-n_steps:]
