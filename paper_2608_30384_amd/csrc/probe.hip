@@ -11,6 +11,7 @@
 // runs take a vector-ALU tile (64 x 64, 4 x 4 outputs per thread) instead.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "rslm_internal.h"
 #include "select_dev.h"
@@ -791,39 +792,64 @@ __global__ void __launch_bounds__(256) k_assign_decide(int64_t n, int shares, Sp
 }
 
 // The listed rows against every centre in float64: workgroups take (64 rows,
-// share of the centres) items, as many shares as fill the chip, so that a few
-// rows cost the time of one tile (us, no row listed against some: 1,024 x 256 by
-// 256 57, 82), which its chain of slabs sets.  About 41 TFLOP/s, so a call whose
-// rows are mostly near ties takes longer than the float32 kernel: 131,072 x 768 by
-// 4,096 2.8 ms with few, 10.5 where the coordinates are 30 times their spread from
-// 0, 25 with every centre twice, float32 6.6 (and 0.6 % of the rows of the second at
-// another centre than the nearest, 33 % at 300 times the spread).  Values are
-// ||c||^2 - 2 <x, c>; the lowest and its lowest id, kNoCentre where no value is
-// below 3.4e38 (and infinite and NaN products as in float32).
-constexpr int kExT = 64, kExK = 32, kExGrid = 1024;
+// share of the centres) items, as many shares as fill the chip.  A share is
+// tiles of 16 TJ centres, 4 x TJ values per thread: TJ = 4 for throughput, TJ = 1
+// and longer slabs up to 256 listed rows, where the chain of one tile's slabs is
+// what a call waits for (22,958 x 475 by 1,581, us: with no row settled here 278, TJ =
+// 4 340, TJ = 1 307).  About 41 TFLOP/s, so a call whose rows are mostly near ties
+// takes longer than the float32 kernel: 131,072 x 768 by 4,096 2.8 ms with few, 10.3
+// where the coordinates are 30 times their spread from 0, 23 with every centre
+// twice, float32 6.6 (and 0.6 % of the rows of the second at another centre than
+// the nearest, 33 % at 300 times the spread).  Values are ||c||^2 - 2 <x, c>,
+// summed over k in order whatever the tile; the lowest and its lowest id, kNoCentre
+// where no value is below 3.4e38 (and infinite and NaN products as in float32).
+constexpr int kExT = 64, kExGrid = 1024;
+constexpr int kExFew = 256;                // rows up to which TJ = 1
 constexpr int kExParts = kExGrid * kExT;   // (row, share) results kept at a time
+constexpr int kExLds = 5120;               // doubles: 32 x (64 + 64) or 64 x (64 + 16)
+__device__ __forceinline__ int exact_tiles(int rows, int nlist) {
+  const int t = rows <= kExFew ? 16 : 64;
+  return (nlist + t - 1) / t;
+}
 __device__ __forceinline__ int exact_shares(int rows, int nlist) {
   const int blocks = (rows + kExT - 1) / kExT;
-  return max(1, min(kExGrid / max(blocks, 1), (nlist + kExT - 1) / kExT));
+  return max(1, min(kExGrid / max(blocks, 1), exact_tiles(rows, nlist)));
 }
-__global__ void __launch_bounds__(256) k_assign_exact(const float *__restrict__ x, int D,
-                                                      const float *__restrict__ cen, int nlist,
-                                                      const double *__restrict__ norm,
-                                                      const int32_t *__restrict__ list,
-                                                      const int32_t *__restrict__ n_listed,
-                                                      double *__restrict__ part_v,
-                                                      int32_t *__restrict__ part_i,
-                                                      int32_t *__restrict__ out_ids) {
-  __shared__ double As[kExK][kExT], Bs[kExK][kExT];
-  const int rows = *n_listed;
+template <int TJ>
+__device__ __forceinline__ void exact_items(const float *__restrict__ x, int D,
+                                            const float *__restrict__ cen, int nlist,
+                                            const double *__restrict__ norm,
+                                            const int32_t *__restrict__ list, int rows, double *lds,
+                                            double *__restrict__ part_v, int32_t *__restrict__ part_i,
+                                            int32_t *__restrict__ out_ids) {
+  constexpr int K = TJ == 1 ? 64 : 32, T = 16 * TJ;
+  constexpr int AE = kExT * K / 256, BE = T * K / 256;   // staged per thread
+  static_assert(K * (kExT + T) <= kExLds, "slabs fit");
+  double(*As)[kExT] = reinterpret_cast<double(*)[kExT]>(lds);
+  double(*Bs)[T] = reinterpret_cast<double(*)[T]>(lds + K * kExT);
   const int blocks = (rows + kExT - 1) / kExT;
   const int shares = exact_shares(rows, nlist);
-  const int tiles = (nlist + kExT - 1) / kExT, per = (tiles + shares - 1) / shares;
+  const int tiles = (nlist + T - 1) / T, per = (tiles + shares - 1) / shares;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int lr = threadIdx.x & 63, lk = (threadIdx.x >> 6) * 8;   // staging: row, first k
+  // staging: row / centre and first k of this thread
+  const int ar = threadIdx.x % kExT, ak = threadIdx.x / kExT * AE;
+  const int br = threadIdx.x % T, bk = threadIdx.x / T * BE;
+  auto load = [&](const float *row, int k, float *v, auto count) {
+    constexpr int N = decltype(count)::value;
+    if (k + N <= D) {
+#pragma unroll
+      for (int q = 0; q < N; q += 4) {
+        const F4u u = *reinterpret_cast<const F4u *>(row + k + q);
+        v[q] = u.x, v[q + 1] = u.y, v[q + 2] = u.z, v[q + 3] = u.w;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < N; ++e) v[e] = k + e < D ? row[min(k + e, D - 1)] : 0.f;
+    }
+  };
   for (int item = blockIdx.x; item < blocks * shares; item += gridDim.x) {
     const int blk = item / shares, share = item - blk * shares;
-    const int64_t arow = int64_t(list[min(blk * kExT + lr, rows - 1)]) * D;
+    const float *arow = x + int64_t(list[min(blk * kExT + ar, rows - 1)]) * D;
     double best[4];
     int32_t bid[4];
 #pragma unroll
@@ -832,54 +858,39 @@ __global__ void __launch_bounds__(256) k_assign_exact(const float *__restrict__ 
       bid[i] = kNoCentre;
     }
     for (int t = share * per; t < min(tiles, share * per + per); ++t) {
-      const int c0 = t * kExT;
-      const int64_t brow = int64_t(min(c0 + lr, nlist - 1)) * D;
-      double acc[4][4] = {};
-      float a[8], b[8];   // the next slab, on its way while one is multiplied
-      auto load = [&](int k0) {
-        if (k0 + kExK <= D) {
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const F4u u = *reinterpret_cast<const F4u *>(x + arow + k0 + lk + 4 * q);
-            const F4u v = *reinterpret_cast<const F4u *>(cen + brow + k0 + lk + 4 * q);
-            a[4 * q] = u.x, a[4 * q + 1] = u.y, a[4 * q + 2] = u.z, a[4 * q + 3] = u.w;
-            b[4 * q] = v.x, b[4 * q + 1] = v.y, b[4 * q + 2] = v.z, b[4 * q + 3] = v.w;
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int k = k0 + lk + e;
-            a[e] = k < D ? x[arow + min(k, D - 1)] : 0.f;
-            b[e] = k < D ? cen[brow + min(k, D - 1)] : 0.f;
-          }
-        }
-      };
-      load(0);
-      for (int k0 = 0; k0 < D; k0 += kExK) {
+      const int c0 = t * T;
+      const float *brow = cen + int64_t(min(c0 + br, nlist - 1)) * D;
+      double acc[4][TJ] = {};
+      float a[AE], b[BE];   // the next slab, on its way while one is multiplied
+      load(arow, ak, a, std::integral_constant<int, AE>());
+      load(brow, bk, b, std::integral_constant<int, BE>());
+      for (int k0 = 0; k0 < D; k0 += K) {
         __syncthreads();   // the previous slab is done with
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          As[lk + e][lr] = double(a[e]);
-          Bs[lk + e][lr] = double(b[e]);
-        }
+        for (int e = 0; e < AE; ++e) As[ak + e][ar] = double(a[e]);
+#pragma unroll
+        for (int e = 0; e < BE; ++e) Bs[bk + e][br] = double(b[e]);
         __syncthreads();
-        if (k0 + kExK < D) load(k0 + kExK);
+        if (k0 + K < D) {
+          load(arow, k0 + K + ak, a, std::integral_constant<int, AE>());
+          load(brow, k0 + K + bk, b, std::integral_constant<int, BE>());
+        }
 #pragma unroll 4
-        for (int kk = 0; kk < kExK; ++kk) {
-          double av[4], bv[4];
+        for (int kk = 0; kk < K; ++kk) {
+          double av[4], bv[TJ];
 #pragma unroll
           for (int i = 0; i < 4; ++i) av[i] = As[kk][ty * 4 + i];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tx * 4 + j];
+          for (int j = 0; j < TJ; ++j) bv[j] = Bs[kk][tx * TJ + j];
 #pragma unroll
           for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
+            for (int j = 0; j < TJ; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
         }
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = c0 + tx * 4 + j;
+      for (int j = 0; j < TJ; ++j) {
+        const int c = c0 + tx * TJ + j;
         const double cn = c < nlist ? norm[c] : double(__builtin_inff());
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -916,15 +927,37 @@ __global__ void __launch_bounds__(256) k_assign_exact(const float *__restrict__ 
     }
   }
 }
-// The listed row at place `at`: its centre.
+__global__ void __launch_bounds__(256) k_assign_exact(const float *__restrict__ x, int D,
+                                                      const float *__restrict__ cen, int nlist,
+                                                      const double *__restrict__ norm,
+                                                      const int32_t *__restrict__ list,
+                                                      const int32_t *__restrict__ n_listed,
+                                                      double *__restrict__ part_v,
+                                                      int32_t *__restrict__ part_i,
+                                                      int32_t *__restrict__ out_ids) {
+  __shared__ double lds[kExLds];
+  const int rows = *n_listed;
+  if (rows <= kExFew) exact_items<1>(x, D, cen, nlist, norm, list, rows, lds, part_v, part_i, out_ids);
+  else exact_items<4>(x, D, cen, nlist, norm, list, rows, lds, part_v, part_i, out_ids);
+}
+// The listed row at place `at`: its centre (by a whole wavefront, in every lane).
 __device__ __forceinline__ int32_t exact_id(int at, int rows, int nlist, const double *part_v,
                                             const int32_t *part_i) {
   const int stride = (rows + kExT - 1) / kExT * kExT, shares = exact_shares(rows, nlist);
   double v = double(kFarthest);
   int32_t id = kNoCentre;
-  for (int s = 0; s < shares; ++s) {
+  for (int s = threadIdx.x & 63; s < shares; s += 64) {   // in increasing order of the centres
     const double ov = part_v[s * stride + at];
     const int32_t oi = part_i[s * stride + at];
+    if (ov < v) {
+      v = ov;
+      id = oi;
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    const double ov = __shfl_xor(v, off, 64);
+    const int32_t oi = __shfl_xor(id, off, 64);
     if (ov < v || (ov == v && oi < id)) {
       v = ov;
       id = oi;
@@ -933,7 +966,8 @@ __device__ __forceinline__ int32_t exact_id(int at, int rows, int nlist, const d
   return id;
 }
 
-// Without distances: the listed rows' centres from their shares.
+// Without distances: the listed rows' centres from their shares, one wavefront
+// per row.
 __global__ void __launch_bounds__(256) k_assign_listed(const int32_t *__restrict__ list,
                                                        const int32_t *__restrict__ n_listed, int nlist,
                                                        const double *__restrict__ part_v,
@@ -941,8 +975,10 @@ __global__ void __launch_bounds__(256) k_assign_listed(const int32_t *__restrict
                                                        int32_t *__restrict__ out_ids) {
   const int rows = *n_listed;
   if (exact_shares(rows, nlist) == 1) return;   // already written
-  for (int at = blockIdx.x * 256 + threadIdx.x; at < rows; at += gridDim.x * 256)
-    out_ids[list[at]] = exact_id(at, rows, nlist, part_v, part_i);
+  for (int at = blockIdx.x * 4 + (threadIdx.x >> 6); at < rows; at += gridDim.x * 4) {
+    const int32_t id = exact_id(at, rows, nlist, part_v, part_i);
+    if ((threadIdx.x & 63) == 0) out_ids[list[at]] = id;
+  }
 }
 
 // With distances: one wavefront per row, the same, and ||x - c||^2 summed in

@@ -209,3 +209,17 @@ def test_workspace_and_pieces_do_not_change_results(R, n, dim, nlist):
     assert lib.ivf_assign_probe(p(x), n, dim, p(c), nlist, 1, R.IVF_ASSIGN_L2, p(ids), C.c_void_p(0), p(ws),
                                 full, stream) == 0
     assert torch.equal(ids, want[0])
+
+
+@pytest.mark.parametrize("n", [128, 256, 257, 4100])
+@pytest.mark.parametrize("dim", [96, 230, 1100])
+def test_rows_settled_in_float64(R, n, dim):
+    """Every row listed (each centre and a copy one rounding away): numbers of rows
+    around where the float64 kernel changes its tile."""
+    g = torch.Generator(device=DEV).manual_seed(n + dim)
+    nlist = 1101
+    c = torch.randn(nlist, dim, generator=g, device=DEV)
+    c[nlist // 2:2 * (nlist // 2)] = c[:nlist // 2] * (1 + 2.0 ** -23)
+    x = c[torch.randint(0, nlist, (n,), generator=g, device=DEV)] + torch.randn(n, dim, generator=g, device=DEV)
+    ids, dist = R.ivf_assign_probe(x, c, 1, R.IVF_ASSIGN_L2)
+    _nearest(x, c, ids, dist)
