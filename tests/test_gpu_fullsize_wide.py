@@ -4,7 +4,7 @@ text-embedding width), 256 lists, 4-bit RSLM with global scaling and two
 rotation passes, SQ8 rescoring codes; a batch of 64 queries, nprobe = 16,
 top-100 from the scan, top-10 after rescoring.
 
-At this width the encoder takes the register path with 12 blocks of 128 and
+At this width the encoder spreads a vector's 12 blocks over four rows of lanes and
 the scan scores each item in two passes of 24 chunks, keeping the partial
 residual dot in the score slot between them.  The oracle checks what it can
 compute one by one: the rotated queries and probe lists, assignment, codes

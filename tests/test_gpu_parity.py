@@ -101,14 +101,14 @@ ENC_CASES = [
     (1024, 3, 2, "global"),
     (256, 2, 2, "global"),
     (64, 4, 0, "global"),      # no rotation
-    # above the register path: the paper's odd-D Compress shape (block-wise
+    # wide: the paper's odd-D Compress shape (block-wise
     # cascade with the overlap block) and the 1,536-d text-embedding width
     (2049, 4, 2, "local"),
     (2049, 3, 2, "global"),
     (1536, 1, 2, "global"),
-    (1536, 4, 2, "global"),    # register path, 12 blocks of 128
+    (1536, 4, 2, "global"),    # rows of lanes, 12 blocks of 128
     (1536, 3, 2, "local"),
-    (2048, 4, 2, "local"),     # register path, 16 blocks of 128
+    (2048, 4, 2, "local"),     # rows of lanes, 16 blocks of 128
 ]
 
 

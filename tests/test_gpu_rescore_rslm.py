@@ -40,15 +40,15 @@ def _t(a, dtype=None):
 
 TWO_CASES = [
     # D, bits1, passes, bits2, mode2, n
-    (768, 4, 2, 2, "global", 700),    # text-embedding shape: register path
-    (256, 4, 1, 2, "global", 333),    # register path, one pass
-    (96, 4, 2, 2, "global", 517),     # overlap block: general path
+    (768, 4, 2, 2, "global", 700),    # text-embedding shape
+    (256, 4, 1, 2, "global", 333),    # one pass
+    (96, 4, 2, 2, "global", 517),     # D < 128: general path
     (128, 2, 1, 4, "global", 300),    # 2-D first stage, 1-D second stage
     (101, 3, 2, 1, "local", 300),     # ragged 4-D second stage, local scale
     (768, 4, 2, 3, "global", 200),    # 3-bit second stage: general path
-    (2049, 4, 2, 2, "global", 150),   # odd D above 1,024: general path, overlap block
-    (1536, 4, 2, 2, "local", 160),    # register path, 12 blocks
-    (2048, 4, 2, 2, "global", 120),   # register path, 16 blocks
+    (2049, 4, 2, 2, "global", 150),   # odd D above 1,024: overlap block
+    (1536, 4, 2, 2, "local", 160),    # 12 blocks
+    (2048, 4, 2, 2, "global", 120),   # 16 blocks
 ]
 
 
